@@ -262,9 +262,10 @@ struct kifmm_plan {
     kifmm::DBuf readback;   // staging words of the tree build's read-backs
     kifmm::DBuf xflag;   // [B + 1] int32: 1 for the boxes the P2L kernel writes (X lists not summed directly)
     kifmm::DBuf n_off, n_idx;   // near lists: U plus the W/X pairs summed point to point
+    kifmm::DBuf n_runs;         // the same as runs of contiguous points (int4, see k_item_fill)
     kifmm::DBuf wf_off, wf_idx; // W lists of the leaf evaluation (the other W pairs)
     kifmm::DBuf xboxes;     // int32 boxes with a non-empty X list
-    kifmm::DBuf items_near, items_far;   // int2 (leaf, first target) work items, heaviest first
+    kifmm::DBuf items_near, items_far;   // work items (int4[2], see k_item_fill; int2 (leaf, first target)), heaviest first
     kifmm::DBuf item_tmp;
     int64_t n_items = 0;
     int64_t n_xboxes = 0;

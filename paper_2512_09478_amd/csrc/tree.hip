@@ -1371,30 +1371,67 @@ __global__ void k_item_count(int B, const int* __restrict__ nl_dev, const int* _
     cnt[i] = (r.y - r.x + 63) / 64;
 }
 
-// One wave per leaf: the lanes sum the near-list source points, then take the
-// leaf's items (up to 64 targets each) one per lane.
+// One wave per leaf: its near list as runs of contiguous sorted points, then
+// its items (up to 64 targets each) one per lane.
+// The runs: the leaf itself first (the only one that must hold pairs at
+// distance zero), then the other entries in list order, neighbouring entries
+// of one image whose point ranges touch joined (siblings do: about half the
+// entries go).  A run is (first point, staged position of the first point,
+// image code, 0); run[nruns] holds the number of staged points.  They start at
+// noff[b] + b, so that every leaf has room for its entries and that last one.
+// A near item is (first target, targets, start of the leaf's runs, their
+// number), (points of the leaf, staged points, 0, 0): one read starts a block.
 __global__ __launch_bounds__(256) void k_item_fill(int nl, const int* __restrict__ leaves,
-                                                   const int2* __restrict__ range, const int* __restrict__ uoff,
-                                                   const int* __restrict__ uidx, const int* __restrict__ woff, int b2,
+                                                   const int2* __restrict__ range, const int* __restrict__ noff,
+                                                   const int* __restrict__ nidx, const int* __restrict__ woff, int b2,
                                                    const int* __restrict__ off, int2* __restrict__ items,
+                                                   int4* __restrict__ near_items, int4* __restrict__ runs,
                                                    uint64_t* __restrict__ key_near, uint64_t* __restrict__ key_far,
                                                    uint32_t* __restrict__ id_near, uint32_t* __restrict__ id_far) {
     const int lane = threadIdx.x & 63, i = blockIdx.x * 4 + int(threadIdx.x >> 6);
     if (i >= nl) return;   // whole wave
     const int b = leaves[i];
     const int2 r = range[b];
-    unsigned long long src = 0;
-    for (int k = uoff[b] + lane; k < uoff[b + 1]; k += 64) {
-        const int2 ra = range[img_box(uidx[k])];
-        src += ra.y - ra.x;
+    const int n0 = noff[b], n1 = noff[b + 1];
+    int4* run = runs + n0 + b;
+    const uint64_t lt = lane_lt_mask();
+    int nr = 1, staged = r.y - r.x;
+    if (lane == 0) run[0] = make_int4(r.x, 0, 0, 0);
+    int last_end = -1, last_code = -1;   // end and image of the entry before this chunk
+    for (int k0 = n0; k0 < n1; k0 += 64) {
+        const int k = k0 + lane;
+        const int e = k < n1 ? nidx[k] : b;
+        const bool use = k < n1 && e != b;   // the leaf itself is run 0
+        const int2 ra = use ? range[img_box(e)] : make_int2(0, 0);
+        const int code = use ? e >> kShiftBits : -1, end = use ? ra.y : -1;
+        int pe = __shfl_up(end, 1, 64), pc = __shfl_up(code, 1, 64);
+        if (lane == 0) {
+            pe = last_end;
+            pc = last_code;
+        }
+        const bool head = use && !(pe == ra.x && pc == code);
+        int incl = ra.y - ra.x;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        const uint64_t hm = __ballot(head);
+        if (head) run[nr + __popcll(hm & lt)] = make_int4(ra.x, staged + incl - (ra.y - ra.x), code, 0);
+        nr += __popcll(hm);
+        staged += __shfl(incl, 63, 64);
+        last_end = __shfl(end, 63, 64);
+        last_code = __shfl(code, 63, 64);
     }
-    for (int o = 32; o >= 1; o >>= 1) src += __shfl_xor(src, o, 64);
+    if (lane == 0) run[nr] = make_int4(0, staged, 0, 0);
+    const unsigned long long src = staged;
     const unsigned long long nfar = (b >= b2 ? 1 : 0) + (woff[b + 1] - woff[b]);
     const int nitem = (r.y - r.x + 63) / 64;
     for (int c = lane; c < nitem; c += 64) {
         const int at = off[i] + c, t0 = r.x + 64 * c;
         const unsigned long long nt = min(64, r.y - t0);
         items[at] = make_int2(b, t0);
+        near_items[2 * size_t(at)] = make_int4(t0, int(nt), n0 + b, nr);
+        near_items[2 * size_t(at) + 1] = make_int4(r.y - r.x, staged, 0, 0);
         const unsigned long long cn = nt * src, cf = nt * nfar * 64;
         // heaviest first: 8-bit keys (one radix pass), descending in log2(cost)
         // in steps of 1/8 (costs within 9 % share a key and keep their order)
@@ -1405,11 +1442,14 @@ __global__ __launch_bounds__(256) void k_item_fill(int nl, const int* __restrict
     }
 }
 
-__global__ void k_item_gather(int n, const int2* __restrict__ items, const uint32_t* __restrict__ idn,
-                              const uint32_t* __restrict__ idf, int2* __restrict__ near, int2* __restrict__ far) {
+__global__ void k_item_gather(int n, const int2* __restrict__ items, const int4* __restrict__ near_items,
+                              const uint32_t* __restrict__ idn, const uint32_t* __restrict__ idf,
+                              int4* __restrict__ near, int2* __restrict__ far) {
     int i = blockIdx.x * TB + threadIdx.x;
     if (i >= n) return;
-    near[i] = items[idn[i]];
+    const size_t k = idn[i];
+    near[2 * size_t(i)] = near_items[2 * k];
+    near[2 * size_t(i) + 1] = near_items[2 * k + 1];
     far[i] = items[idf[i]];
 }
 
@@ -1832,10 +1872,10 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     hipLaunchKernelGGL(k_item_count, dim3(nblocks(B + 1)), dim3(TB), 0, s, B, ol + B, P->leaves.as<int>(),
                        P->bx_range.as<int2>(), icnt);
     exclusive_scan<int>(P, icnt, ioff, B + 1, s);
-    // sizes: leaves, X boxes, items, the input flags, list lengths X, U, W
-    int hs[7];
-    read_ints(P, s, {ol + B, ox + B, ioff + B, bad, xoff + B, uoff + B, woff + B}, hs);
-    const int nl = hs[0], nxb = hs[1], ni = hs[2], hbad = hs[3], nx = hs[4], nu = hs[5], nw = hs[6];
+    // sizes: leaves, X boxes, items, the input flags, list lengths X, U, W, near
+    int hs[8];
+    read_ints(P, s, {ol + B, ox + B, ioff + B, bad, xoff + B, uoff + B, woff + B, noff + B}, hs);
+    const int nl = hs[0], nxb = hs[1], ni = hs[2], hbad = hs[3], nx = hs[4], nu = hs[5], nw = hs[6], nn = hs[7];
     if (hbad & 1)
         throw Error(KIFMM_ERR_INPUT, o.explicit_root ? "non-finite position or point outside the explicit root"
                                                      : "non-finite position");
@@ -1845,27 +1885,30 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     P->n_items = ni;
     // leaf work items, heaviest first
     {
-        P->item_tmp.ensure(size_t(ni) * (8 + 8 + 8 + 4 + 4 + 4 + 4) + 1024);
+        P->item_tmp.ensure(size_t(ni) * (32 + 8 + 8 + 8 + 4 + 4 + 4 + 4) + 1024);
         char* base = P->item_tmp.as<char>();
-        int2* items = reinterpret_cast<int2*>(base);
-        uint64_t* kn = reinterpret_cast<uint64_t*>(base + size_t(ni) * 8);
+        int4* near_items = reinterpret_cast<int4*>(base);
+        int2* items = reinterpret_cast<int2*>(base + size_t(ni) * 32);
+        uint64_t* kn = reinterpret_cast<uint64_t*>(base + size_t(ni) * 40);
         uint64_t* kf = kn + ni;
         uint32_t* idn = reinterpret_cast<uint32_t*>(kf + ni);
         uint32_t* idf = idn + ni;
         uint32_t* vtmp = idf + ni;
         P->tmp_c.ensure(size_t(ni) * 8);
+        P->n_runs.grow((size_t(nn) + size_t(B)) * 16, 0, s);
         hipLaunchKernelGGL(k_item_fill, dim3(nblocks(nl, 4)), dim3(TB), 0, s, nl, P->leaves.as<int>(),
-                           P->bx_range.as<int2>(), noff, P->n_idx.as<int>(), wfoff, b2, ioff, items, kn, kf, idn, idf);
+                           P->bx_range.as<int2>(), noff, P->n_idx.as<int>(), wfoff, b2, ioff, items,
+                           near_items, P->n_runs.as<int4>(), kn, kf, idn, idf);
         // a grid this small runs in one round on the chip, where the order
         // of the items does not matter: leaf order (the identity ids)
         if (ni > kItemOrderMin) {
             radix_sort(P, kn, idn, P->tmp_c.as<uint64_t>(), vtmp, ni, 8, s);
             radix_sort(P, kf, idf, P->tmp_c.as<uint64_t>(), vtmp, ni, 8, s);
         }
-        P->items_near.ensure(size_t(ni) * 8);
+        P->items_near.ensure(size_t(ni) * 32);
         P->items_far.ensure(size_t(ni) * 8);
-        hipLaunchKernelGGL(k_item_gather, dim3(nblocks(ni)), dim3(TB), 0, s, ni, items, idn, idf,
-                           P->items_near.as<int2>(), P->items_far.as<int2>());
+        hipLaunchKernelGGL(k_item_gather, dim3(nblocks(ni)), dim3(TB), 0, s, ni, items, near_items, idn,
+                           idf, P->items_near.as<int4>(), P->items_far.as<int2>());
     }
     // counts (the pair counts are taken on request: count_pairs)
     P->counts[0] = B;
