@@ -17,16 +17,19 @@
 // pair by pair; between leaves two points meet only where their FP32
 // coordinates round to one face, so those pairs run untested and an item whose
 // sum comes out infinite or NaN is done again with every pair tested.
-// The kernels are bound by VALU issue: 14 instructions per untested pair
-// forward (16 tested), so the work beside the pairs is what counts.  Staging
-// copies the runs of contiguous points that the tree build leaves (each wave
-// takes every fourth run): with one list entry of about
-// 25 points at a time and all four waves at each, staging took a quarter of
-// the instructions.  The forward kernel counts 20 FLOP per pair (3 sub, 5 for
-// r^2, rsqrt, 4 for q/r and q/r^3, 7 for the four sums).
+// The kernels are bound by VALU issue (14 instructions per untested pair
+// forward, 16 tested; about 3 cycles each) once the reads are out of the way:
+// a wave copies 64 staged positions at a time out of the runs of contiguous
+// points that the tree build leaves, and the next batch is read while one is
+// summed.  Reading box by box between barriers left the waves waiting for 58 %
+// of their time (1M clustered points, alone: 0.84 ms forward and 1.36 ms
+// backward; now 0.60 and 1.07 ms, 42 and 23 TFLOP/s at 20 FLOP per pair:
+// 3 sub, 5 for r^2, rsqrt, 4 for q/r and q/r^3, 7 for the four sums).
 #include <float.h>
 #include <math.h>
 
+#include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "common.h"
@@ -41,9 +44,21 @@ constexpr int NF_ONE = 512, NF_GRAD = 768, NF_TWO = 512;
 // near-field blocks wanted before the items of a small system are no longer divided
 constexpr int kNearFill = 1024;
 
+// Near-field blocks per CU.  Far-field kernels run beside it: with the CUs
+// full of near-field blocks (eight) a far-field block waits until the near
+// field's last blocks start, with four it starts at once and the far field's
+// matrix products run beside the near field's vector instructions (524,288
+// uniform points, evaluation and adjoint: 2.48 ms with four, 2.58 with three,
+// 2.63 with six, 2.65 uncapped; 262,147 with field gradient 0.77 against 0.77,
+// 0.97 and 1.01 ms).  With many points per leaf the near field is most of the
+// work (8.4M Plummer points, p = 8: 10 of 17 ms) and takes six.
+constexpr int kNearBlocks = 4, kNearBlocksDense = 6, kNearDense = 64;
+
+// The gathers precede the near field on the caller's stream and zero its counter.
 __global__ void k_gather(int64_t N, const float4* __restrict__ xs, const int* __restrict__ perm,
-                         const float* __restrict__ q, float4* __restrict__ pts) {
+                         const float* __restrict__ q, float4* __restrict__ pts, int* __restrict__ taken) {
     int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
+    if (i == 0) *taken = 0;
     if (i >= N) return;
     float4 x = xs[i];
     x.w = q ? q[perm[i]] : 0.f;
@@ -51,8 +66,9 @@ __global__ void k_gather(int64_t N, const float4* __restrict__ xs, const int* __
 }
 
 __global__ void k_gather_adj(int64_t N, const int* __restrict__ perm, const float* __restrict__ gu,
-                             const float* __restrict__ ge, float4* __restrict__ src2) {
+                             const float* __restrict__ ge, float4* __restrict__ src2, int* __restrict__ taken) {
     int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
+    if (i == 0) *taken = 0;
     if (i >= N) return;
     int j = perm[i];
     src2[i] = make_float4(gu ? gu[j] : 0.f, ge ? ge[3 * size_t(j)] : 0.f, ge ? ge[3 * size_t(j) + 1] : 0.f,
@@ -123,8 +139,9 @@ __device__ inline float group_sum(float v, int slice, int S) {
 // What the near-field kernels read beside the points.
 struct NearArgs {
     const int4* items;   // two words an item, see k_item_fill
-    int parts;           // blocks per item, each with an equal part of its targets
+    int units, parts;    // units of work: every item in `parts` equal parts of its targets
     const int4* runs;    // runs of contiguous source points, see k_item_fill
+    int* taken;          // units taken beyond the grid's first round
     float cell;          // periodic cell side (image shifts)
 };
 
@@ -139,6 +156,7 @@ struct NearShared {
         float red[4][NV][64];
     };
     int key[KEY ? CAP : 1];
+    int next[2];   // the block's next unit, in turns
 };
 
 // The source points a thread copies of one batch.
@@ -235,50 +253,61 @@ __device__ inline bool near_finish(float (&v)[NV], const NearMap& m, float (*red
     return (threadIdx.x >> 6) == 0 && m.act && m.slice == 0;
 }
 
-// The item of a near-field block.  load(i, act) reads target i, pair(chk, j, v)
+// The units of a near-field block.  load(i, act) reads target i, pair(chk, j, v)
 // adds staged source j to the sums v, store(i, v) writes the totals.
 // The next batch of sources is read into registers while the present one is
-// summed.
+// summed.  Blocks take their later units from a counter, so that a grid smaller
+// than the work keeps its balance; a unit's arithmetic does not depend on the
+// block that does it.
 template <int CAP, bool TWO, bool KEY, int NV, int UNROLL, class Load, class Pair, class Store>
-__device__ inline void near_item(const NearArgs& a, const float4* __restrict__ pts, const float4* __restrict__ src2,
-                                 const int* __restrict__ ckey, NearShared<CAP, TWO, KEY, NV>& sh, Load load, Pair pair,
-                                 Store store) {
+__device__ inline void near_units(const NearArgs& a, const float4* __restrict__ pts, const float4* __restrict__ src2,
+                                  const int* __restrict__ ckey, NearShared<CAP, TWO, KEY, NV>& sh, Load load,
+                                  Pair pair, Store store) {
     static_assert(sizeof(float) * 4 * NV * 64 <= sizeof(float4) * CAP * (TWO ? 2 : 1), "reduction fits the staging");
-    const int unit = blockIdx.x / unsigned(a.parts), part = blockIdx.x % unsigned(a.parts);
-    const int4 i0 = a.items[2 * size_t(unit)], i1 = a.items[2 * size_t(unit) + 1];
-    const int per = (i0.y + a.parts - 1) / a.parts, t0 = part * per, nt = min(per, i0.y - t0);
-    if (nt <= 0) return;   // whole block
-    const int4* run = a.runs + i0.z;
-    const int nr = i0.w, own = KEY ? 0 : i1.x, total = i1.y;
     const int lane = threadIdx.x & 63;
-    const int4 d = run[min(lane, nr)];
-    const int dn = run[min(lane + 1, nr)].y;
-    const NearMap nm = near_map(i0.x + t0, nt);
-    load(nm.i, nm.act);
-    float v[NV];
-    // first with only the leaf's own points tested for distance zero (with
-    // keys, none: they tell the self pair), then, if a sum is not finite, all
-    for (int pass = 0; pass < 2; ++pass) {
+    int unit = blockIdx.x;
+    int4 i0 = a.items[2 * size_t(unit / a.parts)], i1 = a.items[2 * size_t(unit / a.parts) + 1];
+    for (int turn = 0; unit < a.units; turn ^= 1) {
+        const int per = (i0.y + a.parts - 1) / a.parts, t0 = (unit % a.parts) * per, nt = min(per, i0.y - t0);
+        const int4* run = a.runs + i0.z;
+        const int nr = i0.w, own = KEY ? 0 : i1.x, total = nt > 0 ? i1.y : 0;
+        const int4 d = run[min(lane, nr)];
+        const int dn = run[min(lane + 1, nr)].y;
+        int next = a.units;
+        if (threadIdx.x == 0 && gridDim.x < unsigned(a.units)) next = int(gridDim.x) + atomicAdd(a.taken, 1);
+        const NearMap nm = near_map(i0.x + t0, max(nt, 1));
+        load(nm.i, nm.act && nt > 0);
+        float v[NV];
+        // first with only the leaf's own points tested for distance zero (with
+        // keys, none: they tell the self pair), then, if a sum is not finite, all
+        for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-        for (int q = 0; q < NV; ++q) v[q] = 0.f;
-        Staged<CAP, TWO, KEY> st;
-        st.read(run, nr, d, dn, 0, min(CAP, total), a.cell, pts, src2, ckey);
-        for (int b0 = 0; b0 < total; b0 += CAP) {
-            const int m = min(CAP, total - b0);
-            const int tested = pass ? m : min(max(own - b0, 0), m);
-            __syncthreads();
-            st.write(sh, m);
-            __syncthreads();
-            if (b0 + CAP < total)
-                st.read(run, nr, d, dn, b0 + CAP, min(CAP, total - b0 - CAP), a.cell, pts, src2, ckey);
-            for_sources<UNROLL>(nm, 0, tested, [&](int j) { pair(std::true_type{}, j, v); });
-            for_sources<UNROLL>(nm, tested, m, [&](int j) { pair(std::false_type{}, j, v); });
+            for (int q = 0; q < NV; ++q) v[q] = 0.f;
+            Staged<CAP, TWO, KEY> st;
+            st.read(run, nr, d, dn, 0, min(CAP, total), a.cell, pts, src2, ckey);
+            for (int b0 = 0; b0 < total; b0 += CAP) {
+                const int m = min(CAP, total - b0);
+                const int tested = pass ? m : min(max(own - b0, 0), m);
+                __syncthreads();
+                st.write(sh, m);
+                __syncthreads();
+                if (b0 + CAP < total)
+                    st.read(run, nr, d, dn, b0 + CAP, min(CAP, total - b0 - CAP), a.cell, pts, src2, ckey);
+                for_sources<UNROLL>(nm, 0, tested, [&](int j) { pair(std::true_type{}, j, v); });
+                for_sources<UNROLL>(nm, tested, m, [&](int j) { pair(std::false_type{}, j, v); });
+            }
+            // every sum of v[0] has 1/r as a factor, and any number times
+            // infinity is not finite
+            if (threadIdx.x == 0) sh.next[turn] = next;
+            if (!__syncthreads_or(pass == 0 && nm.act && !(fabsf(v[0]) <= FLT_MAX))) break;
         }
-        // every sum of v[0] has 1/r as a factor, and any number times infinity
-        // is not finite
-        if (pass || !__syncthreads_or(nm.act && !(fabsf(v[0]) <= FLT_MAX))) break;
+        unit = sh.next[turn];
+        if (unit < a.units) {   // read ahead of the reduction
+            i0 = a.items[2 * size_t(unit / a.parts)];
+            i1 = a.items[2 * size_t(unit / a.parts) + 1];
+        }
+        if (near_finish<NV>(v, nm, sh.red) && nt > 0) store(nm.i, v);
     }
-    if (near_finish<NV>(v, nm, sh.red)) store(nm.i, v);
 }
 
 // EXCL: pairs whose clump keys (ckey, sorted) are equal are left out, which
@@ -289,7 +318,7 @@ __global__ __launch_bounds__(256, 8) void k_p2p(NearArgs a, const float4* __rest
     __shared__ NearShared<NF_ONE, false, EXCL, 4> sh;
     float4 x;
     int ck = 0;
-    near_item<NF_ONE, false, EXCL, 4, 4>(
+    near_units<NF_ONE, false, EXCL, 4, 4>(
         a, pts, nullptr, ckey, sh,
         [&](int i, bool act) {
             x = act ? pts[i] : make_float4(0, 0, 0, 0);
@@ -317,7 +346,7 @@ __global__ __launch_bounds__(256) void k_p2p_dip(NearArgs a, const float4* __res
                                                  float4* __restrict__ nearv) {
     __shared__ NearShared<NF_TWO, true, false, 4> sh;
     float4 x;
-    near_item<NF_TWO, true, false, 4, 2>(
+    near_units<NF_TWO, true, false, 4, 2>(
         a, pts, src2, nullptr, sh, [&](int i, bool act) { x = act ? pts[i] : make_float4(0, 0, 0, 0); },
         [&](auto chk, int j, float(&v)[4]) {   // v: u, ex, ey, ez
             const float4 y = sh.p[j];
@@ -349,7 +378,7 @@ __global__ __launch_bounds__(256) void k_p2p_grad(NearArgs a, const float4* __re
     constexpr int CAP = DIP ? NF_TWO : NF_GRAD;
     __shared__ NearShared<CAP, DIP, false, 10> sh;
     float4 x;
-    near_item<CAP, DIP, false, 10, DIP ? 2 : 4>(
+    near_units<CAP, DIP, false, 10, DIP ? 2 : 4>(
         a, pts, src2, nullptr, sh, [&](int i, bool act) { x = act ? pts[i] : make_float4(0, 0, 0, 0); },
         [&](auto chk, int j, float(&v)[10]) {   // v: u, E xyz, dE/dx xx yy zz xy xz yz
             const float4 y = sh.p[j];
@@ -424,7 +453,7 @@ __global__ __launch_bounds__(256, 7) void k_p2p_bwd(NearArgs na, const float4* _
     // psi is kept as its two sums (v[7] ubar_j / r, v[8] r.Ebar_j / r^3)
     float4 x, a;
     int ck = 0;
-    near_item<NF_TWO, true, EXCL, 9, 1>(
+    near_units<NF_TWO, true, EXCL, 9, 1>(
         na, pts, src2, ckey, sh,
         [&](int i, bool act) {
             x = act ? pts[i] : make_float4(0, 0, 0, 0);
@@ -469,8 +498,9 @@ __global__ __launch_bounds__(256, 7) void k_p2p_bwd(NearArgs na, const float4* _
 // from stk where a box's sources are summed.
 __global__ void k_gather_stokes(int64_t N, const float4* __restrict__ xs, const int* __restrict__ perm,
                                 const float* __restrict__ f, int pass, float4* __restrict__ pts,
-                                float4* __restrict__ src2, float4* __restrict__ stk) {
+                                float4* __restrict__ src2, float4* __restrict__ stk, int* __restrict__ taken) {
     int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
+    if (pass == 0 && i == 0) *taken = 0;   // the near field of pass 0 may still run in pass 1
     if (i >= N) return;
     const size_t j = size_t(perm[i]);
     const float fx = f[3 * j], fy = f[3 * j + 1], fz = f[3 * j + 2];
@@ -495,7 +525,7 @@ __global__ __launch_bounds__(256) void k_p2p_stokes(NearArgs a, const float4* __
                                                     float4* __restrict__ out) {
     __shared__ NearShared<NF_TWO, true, false, 4> sh;
     float4 x;
-    near_item<NF_TWO, true, false, 4, 1>(
+    near_units<NF_TWO, true, false, 4, 1>(
         a, xs, stk, nullptr, sh, [&](int i, bool act) { x = act ? xs[i] : make_float4(0, 0, 0, 0); },
         [&](auto chk, int j, float(&v)[4]) {
             const float4 y = sh.p[j];
@@ -517,13 +547,29 @@ struct NearLaunch {
     dim3 grid;
 };
 
+int device_cus() {
+    static std::atomic<int> cus[kMaxDevices];
+    int dev = 0;
+    KIFMM_HIP(hipGetDevice(&dev));
+    const bool kept = dev >= 0 && dev < kMaxDevices;
+    int n = kept ? cus[dev].load(std::memory_order_relaxed) : 0;
+    if (n == 0) {
+        KIFMM_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        if (kept) cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 NearLaunch near_launch(kifmm_plan* P, bool images = true) {
-    // few items: several blocks each, until the chip has work for a full round
-    // of eight blocks per CU (2,048)
+    // few items: in parts, until the chip has work for half a round of eight
+    // blocks per CU
     int parts = 1;
     while (parts < 8 && P->n_items * parts < kNearFill) parts *= 2;
-    return NearLaunch{NearArgs{P->items_near.as<int4>(), parts, P->n_runs.as<int4>(), images ? float(P->side) : 0.f},
-                      dim3(unsigned(P->n_items * parts))};
+    const int units = int(P->n_items) * parts;
+    const int per_cu = P->N > int64_t(kNearDense) * P->nleaves ? kNearBlocksDense : kNearBlocks;
+    return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->n_runs.as<int4>(), P->near_taken.as<int>(),
+                               images ? float(P->side) : 0.f},
+                      dim3(unsigned(std::min(units, device_cus() * per_cu)))};
 }
 
 }  // namespace
@@ -531,15 +577,16 @@ NearLaunch near_launch(kifmm_plan* P, bool images = true) {
 void launch_gather(kifmm_plan* P, const float* charges, const float* gpot, const float* gfield, bool adjoint,
                    hipStream_t s, bool points) {
     const int64_t N = P->N;
+    int* taken = static_cast<int*>(P->near_taken.ensure(sizeof(int)));
     if (charges || points) {
         P->pts.ensure(size_t(N) * 16);
         hipLaunchKernelGGL(k_gather, dim3(unsigned((N + 255) / 256)), dim3(256), 0, s, N, P->xs.as<float4>(),
-                           P->perm.as<int>(), charges, P->pts.as<float4>());
+                           P->perm.as<int>(), charges, P->pts.as<float4>(), taken);
     }
     if (adjoint) {
         P->src2.ensure(size_t(N) * 16);
         hipLaunchKernelGGL(k_gather_adj, dim3(unsigned((N + 255) / 256)), dim3(256), 0, s, N, P->perm.as<int>(), gpot,
-                           gfield, P->src2.as<float4>());
+                           gfield, P->src2.as<float4>(), taken);
     }
 }
 
@@ -550,7 +597,7 @@ void launch_gather_stokes(kifmm_plan* P, const float* forces, int pass, hipStrea
     P->stk.ensure(size_t(N) * 16);
     hipLaunchKernelGGL(k_gather_stokes, dim3(unsigned((N + 255) / 256)), dim3(256), 0, s, N, P->xs.as<float4>(),
                        P->perm.as<int>(), forces, pass, P->pts.as<float4>(), P->src2.as<float4>(),
-                       P->stk.as<float4>());
+                       P->stk.as<float4>(), static_cast<int*>(P->near_taken.ensure(sizeof(int))));
 }
 
 void launch_p2p_forward(kifmm_plan* P, hipStream_t s, bool excl) {
