@@ -153,7 +153,7 @@ struct Operators {
 struct M2LBasis {
     int k = 0, kp = 0;
     std::vector<double> sigma;   // singular values of [M2L(d_1) ... M2L(d_316)] (unit operators), descending
-    DBuf q;           // float [NP][kp]: Q row-major, zero-padded (operand of the expansion psi += Q psi_k)
+    DBuf q;           // float [NP][kp]: Q, zero-padded, in chain order (operand of the expansion psi += Q psi_k)
     DBuf qt;          // float [kp][NP]: Q^T row-major, zero-padded (operand of the projection phi_k = Q^T phi)
     DBuf core_f32;    // [316] cores in gather-fragment order at kp (FP32)
     DBuf core_bf16;   // the same, bf16 hi/lo

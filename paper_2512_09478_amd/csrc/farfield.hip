@@ -24,8 +24,8 @@
 #include <stdlib.h>
 
 #include <algorithm>
-
 #include <functional>
+#include <type_traits>
 
 #include "common.h"
 
@@ -37,6 +37,12 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int WAVES = 4;
+
+// Boxes up to which the check-to-equivalent map takes one or two column blocks
+// of 16 boxes per block, and non-leaves of a level up to which M2M spreads its
+// row blocks as widely as they go
+constexpr int kC2eOne = 4096, kC2eTwo = 32768;
+constexpr int kM2mFew = 1024;
 
 struct BoxGeom {
     double lo[3];
@@ -95,108 +101,6 @@ __device__ inline void store_acc(const v4f* acc, float* __restrict__ col, int la
 #pragma unroll
     for (int rb = 0; rb < NP / 16; ++rb)
         *reinterpret_cast<float4*>(col + rb * 16 + 4 * g) = make_float4(acc[rb][0], acc[rb][1], acc[rb][2], acc[rb][3]);
-}
-
-// acc += A * b, A row-major NP x NP (FP32), b this lane's source column (or null = 0)
-template <int NP>
-__device__ inline void gemm_f32(v4f* acc, const float* __restrict__ A, const float* __restrict__ b, int lane) {
-    const int g = lane >> 4, r = lane & 15;
-    for (int kc = 0; kc < NP; kc += 32) {
-        float bv[8];
-        if (b) {
-            float4 b0 = *reinterpret_cast<const float4*>(b + kc + 8 * g);
-            float4 b1 = *reinterpret_cast<const float4*>(b + kc + 8 * g + 4);
-            bv[0] = b0.x; bv[1] = b0.y; bv[2] = b0.z; bv[3] = b0.w;
-            bv[4] = b1.x; bv[5] = b1.y; bv[6] = b1.z; bv[7] = b1.w;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) bv[i] = 0.f;
-        }
-#pragma unroll
-        for (int rb = 0; rb < NP / 16; ++rb) {
-            const float* ap = A + size_t(rb * 16 + r) * NP + kc + 8 * g;
-            float4 a0 = *reinterpret_cast<const float4*>(ap);
-            float4 a1 = *reinterpret_cast<const float4*>(ap + 4);
-            v4f c = acc[rb];
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, bv[0], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, bv[1], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.z, bv[2], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.w, bv[3], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, bv[4], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, bv[5], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.z, bv[6], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.w, bv[7], c, 0, 0, 0);
-            acc[rb] = c;
-        }
-    }
-}
-
-// acc += A * b with A and b split into bf16 hi/lo (A pre-split, b split here)
-template <int NP>
-__device__ inline void gemm_bf16x3(v4f* acc, const __bf16* __restrict__ Ahi, const __bf16* __restrict__ Alo,
-                                   const float* __restrict__ b, int lane) {
-    const int g = lane >> 4, r = lane & 15;
-    for (int kc = 0; kc < NP; kc += 32) {
-        v8bf bh, bl;
-        if (b) {
-            float4 b0 = *reinterpret_cast<const float4*>(b + kc + 8 * g);
-            float4 b1 = *reinterpret_cast<const float4*>(b + kc + 8 * g + 4);
-            float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __bf16 h = (__bf16)bv[i];
-                bh[i] = h;
-                bl[i] = (__bf16)(bv[i] - (float)h);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                bh[i] = (__bf16)0.f;
-                bl[i] = (__bf16)0.f;
-            }
-        }
-#pragma unroll
-        for (int rb = 0; rb < NP / 16; ++rb) {
-            size_t off = size_t(rb * 16 + r) * NP + kc + 8 * g;
-            v8bf ah = *reinterpret_cast<const v8bf*>(Ahi + off);
-            v8bf al = *reinterpret_cast<const v8bf*>(Alo + off);
-            v4f c = acc[rb];
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, c, 0, 0, 0);
-            acc[rb] = c;
-        }
-    }
-}
-
-// out += A * T, with T given in accumulator layout (row k = 16 rb + 4 g + r)
-template <int NP>
-__device__ inline void gemm_f32_chain(v4f* out, const float* __restrict__ A, const v4f* T, int lane) {
-    const int g = lane >> 4, r = lane & 15;
-#pragma unroll
-    for (int ob = 0; ob < NP / 16; ++ob) {
-        v4f c = out[ob];
-        const float* ap = A + size_t(ob * 16 + r) * NP + 4 * g;
-#pragma unroll
-        for (int rb = 0; rb < NP / 16; ++rb) {
-            float4 a = *reinterpret_cast<const float4*>(ap + rb * 16);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, T[rb][0], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, T[rb][1], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, T[rb][2], c, 0, 0, 0);
-            c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, T[rb][3], c, 0, 0, 0);
-        }
-        out[ob] = c;
-    }
-}
-
-// phi = Vm * (W1 * psi): the factored check-to-equivalent map on an accumulator
-template <int NP>
-__device__ inline void c2e_apply(v4f* acc, const float* __restrict__ W1, const float* __restrict__ Vm, int lane) {
-    v4f t[NP / 16];
-    zero_acc<NP>(t);
-    gemm_f32_chain<NP>(t, W1, acc, lane);
-    zero_acc<NP>(acc);
-    gemm_f32_chain<NP>(acc, Vm, t, lane);
 }
 
 // ------------------------------------------------------------------ P2M / P2L
@@ -593,201 +497,333 @@ __global__ __launch_bounds__(256, STK ? 2 : 3) void k_m2l(TaskTable tt, int nblk
                       lane);
 }
 
-// ------------------------------------------------------------------ upward and downward translations
-// Upward (UP): for the boxes list[b0 .. b0+nb) (the leaves of every level, or
-// the non-leaves of one), psi = P2M result (leaves) or sum_o M2M[o]
-// phi_u(child o) (non-leaves), then phi_u = V (W1 psi).
-// Downward: for the children at octant o of non-leaf parents, psi = the summed
-// M2L partials (+ X list) + L2L[o] phi_d(parent) (from level 3), then
-// phi_d = U (W1d psi).
-// A block holds 16 boxes (one MFMA column block) and its four waves split the
-// NP/16 output row blocks (wave w owns rb = w, w + 4, ...), so that even a
-// level with a few boxes is spread over several SIMDs.  The operators (under
-// 1 MB) are read as MFMA fragments straight from L2.  The chained
-// check-to-equivalent factors need the whole intermediate vector: it is
-// exchanged through LDS in accumulator layout.
-// STK (the Stokeslet's fourth charge in per-box frames): every gathered
-// source column adds (c_source - c_target) times the same box's densities of
-// the three force components (s0, s1, s2), which moves it into the target's
-// frame.
-template <int NP, bool UP, bool STK>
-__global__ __launch_bounds__(256) void k_updown(int nblk, int b0, int nb, const int* __restrict__ list, int nl_start,
-                                                int nl_count, int has_l2l,
-                                                const int* __restrict__ nonleaf, const int2* __restrict__ child,
-                                                const int* __restrict__ leafflag, const float* __restrict__ psi_in,
-                                                int nsplit, size_t split_stride, const float* __restrict__ gsrc,
-                                                float* __restrict__ out, const uint4* __restrict__ gops,
-                                                const uint4* __restrict__ w1c, const uint4* __restrict__ vc,
-                                                const int4* __restrict__ anchor, BoxGeom geo,
-                                                const float* __restrict__ s0, const float* __restrict__ s1,
-                                                const float* __restrict__ s2) {
-    constexpr int RB = NP / 16, KC = NP / 32, NR = (RB + 3) / 4;
-    __shared__ v4f xa[RB][64];
+// ------------------------------------------------------------------ check-to-equivalent maps
+// phi = V (W1 psi).  The two factors stay apart: W1 carries the inverse
+// singular values (up to 1e7), and only the factored product keeps FP32
+// rounding out of the density's potential.
+// Upward (DOWN = false): the boxes list[b0 .. b0+nb) (the leaves of every
+// level, or the non-leaves of one), psi the P2M or M2M result.  Downward: the children at octant o of the non-leaf boxes
+// list[b0 .. b0+nb) of one level, psi = the sum of nsplit M2L partials
+// split_stride apart (with KP > 0 expanded out of the compressed M2L's basis,
+// psi = Q psi_k, plus the X-list part xpsi of the boxes flagged in xflag)
+// + L2L[o] phi(parent) when l2l is set.
+// A block holds 16 CB boxes (CB MFMA column blocks) and each of its WV waves
+// owns NR output row blocks; the right factors are exchanged through LDS in
+// accumulator layout, the operators (0.1-0.4 MB each) come from L2.  With few
+// boxes the launch is one chain of dependent reads and MFMA steps, so it takes
+// as many waves as there are row blocks (CB = NR = 1); with many it is bound by
+// operator reads and FP32 MFMA issue, and CB column blocks share each operator
+// fragment.  Registers stay few in the first form: a block of ten waves starts
+// only on a CU with room for all of them beside the near field's (holding the
+// factors in registers ahead of the data needed 100 a wave, took as long alone
+// and waited for the whole near field beside it).  The order of every sum is the same in all forms:
+// rounding of the check potentials is amplified by the map, up to 7e-5 of the
+// field in the deep leaves of a one-signed system, so a form that added in
+// another order would show.
+// STK (the Stokeslet's fourth charge in per-box frames): the parent's column
+// adds (c_parent - c_child) times its densities of the three force components
+// (s0, s1, s2), which moves it into the child's frame.
+constexpr int chain_waves(int np, bool wide) {
+    return np == 32 ? 2 : np == 64 ? 4 : np == 128 ? (wide ? 8 : 4) : np == 160 ? (wide ? 10 : 5) : np == 224 ? 7 : 10;
+}
+
+template <int NP, int WV, int CB, int KP, bool DOWN, bool STK>
+__global__ __launch_bounds__(64 * WV) void k_c2e(int nblk, int b0, int nb, const int* __restrict__ list,
+                                                 const int2* __restrict__ child, const float* __restrict__ psi,
+                                                 int nsplit, size_t split_stride, const float* __restrict__ xpsi,
+                                                 const int* __restrict__ xflag, const uint4* __restrict__ qc,
+                                                 const uint4* __restrict__ l2l, const uint4* __restrict__ w1c,
+                                                 const uint4* __restrict__ vc, float* phi,
+                                                 const int4* __restrict__ anchor, BoxGeom geo,
+                                                 const float* __restrict__ s0, const float* __restrict__ s1,
+                                                 const float* __restrict__ s2) {
+    constexpr int RB = NP / 16, KC = NP / 32, NR = RB / WV;
+    constexpr int IW = KP ? KP : NP, IB = IW / 16;   // input width and its row blocks
+    static_assert(NR * WV == RB, "waves own whole row blocks");
+    __shared__ v4f xa[RB > IB ? RB : IB][CB][64];
     __builtin_amdgcn_s_setprio(2);   // issue ahead of the near-field waves sharing the SIMD
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g4 = 4 * (lane >> 4), g8 = 8 * (lane >> 4);
     const int bid = xcd_remap(blockIdx.x, nblk);
-    const int g4 = 4 * (lane >> 4), g8 = 8 * (lane >> 4);
-    int tgt = -1, par = -1, cmask = 0, cfirst = 0, o = 0;
-    if (UP) {
-        const int idx = bid * 16 + (lane & 15);
+    const int o = DOWN ? bid % 8 : 0, grp = DOWN ? bid / 8 : bid;
+    int tgt[CB], par[CB];
+    bool any = false;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int idx = (grp * CB + cb) * 16 + (lane & 15);
+        tgt[cb] = par[cb] = -1;
         if (idx < nb) {
-            tgt = list[b0 + idx];
-            if (!leafflag[tgt]) {
-                const int2 ch = child[tgt];
-                cfirst = ch.x;
-                cmask = ch.y;
+            const int box = list[b0 + idx];
+            if (DOWN) {
+                const int2 ch = child[box];
+                if ((ch.y >> o) & 1) {
+                    tgt[cb] = ch.x + __popc(ch.y & ((1 << o) - 1));
+                    par[cb] = box;
+                }
+            } else {
+                tgt[cb] = box;
             }
         }
-    } else {
-        o = bid % 8;
-        const int slot = (bid / 8) * 16 + (lane & 15);
-        if (slot < nl_count) {
-            const int Pb = nonleaf[nl_start + slot];
-            const int2 ch = child[Pb];
-            if ((ch.y >> o) & 1) {
-                tgt = ch.x + __popc(ch.y & ((1 << o) - 1));
-                par = Pb;
+        any |= tgt[cb] >= 0;
+    }
+    if (!__ballot(any)) return;   // every wave holds the same columns: uniform over the block
+    // the sum of the partials, for input row block rb
+    auto load_sum = [&](int rb, int cb) {
+        v4f t = v4f{0.f, 0.f, 0.f, 0.f};
+        if (tgt[cb] >= 0) {
+            const float* col = psi + size_t(tgt[cb]) * IW + rb * 16 + g4;
+#pragma unroll (CB == 1 ? 8 : 4)
+            for (int sp = 0; sp < (DOWN ? nsplit : 1); ++sp) {
+                const float4 v = *reinterpret_cast<const float4*>(col + sp * split_stride);
+                t += v4f{v.x, v.y, v.z, v.w};
             }
         }
-    }
-    // the gather terms any column of the block needs (every wave holds the
-    // same 16 columns, so this is uniform over the block)
-    int flags = 0;
-    if (UP) {
-#pragma unroll
-        for (int oc = 0; oc < 8; ++oc)
-            if (__ballot((cmask >> oc) & 1)) flags |= 1 << oc;
-    } else {
-        flags = __ballot(tgt >= 0) ? 1 : 0;
-        if (!flags) return;
-    }
-    const float* col0 = tgt >= 0 ? psi_in + size_t(tgt) * NP : nullptr;
-    v4f acc[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        const int rb = wave + 4 * i;
-        acc[i] = v4f{0.f, 0.f, 0.f, 0.f};
-        if (rb < RB && col0 && !(UP && cmask)) {
-            for (int sp = 0; sp < (UP ? 1 : nsplit); ++sp) {
-                const float4 v = *reinterpret_cast<const float4*>(col0 + sp * split_stride + rb * 16 + g4);
-                acc[i] += v4f{v.x, v.y, v.z, v.w};
-            }
-        }
-    }
-    // gather: acc += T[op] src (T in fragment order [kc][rb][2][64]); the
-    // steps (term, 32-column chunk) run with the next step's fragments and
-    // source values already in flight
-    const int nterm = UP ? __popc(flags) : (has_l2l ? 1 : 0);
-    const int nst = nterm * KC;
-    auto step_src = [&](int st, const uint4*& A, const float*& b, int& sb) {
-        const int t = st / KC, kc = st % KC;
-        int op = o;
-        if (UP) {
-            int f = flags;
-            for (int k = 0; k < t; ++k) f &= f - 1;
-            op = __builtin_ctz(f);
-        }
-        sb = -1;
-        if (UP) {
-            if ((cmask >> op) & 1) sb = cfirst + __popc(cmask & ((1 << op) - 1));
-        } else if (par >= 0) {
-            sb = par;
-        }
-        A = gops + (size_t(op) * KC + kc) * RB * 128 + lane;
-        b = sb >= 0 ? gsrc + size_t(sb) * NP + kc * 32 + g8 : nullptr;
+        return t;
     };
-    uint4 an[NR][2];
-    float bn[8];
-    auto fetch = [&](int st) {
-        const uint4* A;
-        const float* b;
-        int sb;
-        step_src(st, A, b, sb);
-        load8(bn, b);
-        if constexpr (STK) {
-            if (sb >= 0) {
-                const size_t o8 = size_t(sb) * NP + (st % KC) * 32 + g8;
-                float bx[8], by[8], bz[8], d[3];
-                load8(bx, s0 + o8);
-                load8(by, s1 + o8);
-                load8(bz, s2 + o8);
-                centre_diff(geo, anchor[sb], anchor[tgt], d);
-#pragma unroll
-                for (int k = 0; k < 8; ++k) bn[k] += d[0] * bx[k] + d[1] * by[k] + d[2] * bz[k];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            const int rb = wave + 4 * i;
-            if (rb < RB) {
-                an[i][0] = A[rb * 128];
-                an[i][1] = A[rb * 128 + 64];
-            }
-        }
-    };
-    if (nst > 0) fetch(0);
-    for (int st = 0; st < nst; ++st) {
-        uint4 ac[NR][2];
-        float bc[8];
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            ac[i][0] = an[i][0];
-            ac[i][1] = an[i][1];
-        }
-#pragma unroll
-        for (int k = 0; k < 8; ++k) bc[k] = bn[k];
-        if (st + 1 < nst) fetch(st + 1);
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            if (wave + 4 * i < RB) {
-                const float a[8] = {__uint_as_float(ac[i][0].x), __uint_as_float(ac[i][0].y),
-                                    __uint_as_float(ac[i][0].z), __uint_as_float(ac[i][0].w),
-                                    __uint_as_float(ac[i][1].x), __uint_as_float(ac[i][1].y),
-                                    __uint_as_float(ac[i][1].z), __uint_as_float(ac[i][1].w)};
-                v4f c = acc[i];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], bc[k], c, 0, 0, 0);
-                acc[i] = c;
-            }
-        }
-    }
-    // chained factors: acc = V (W1 acc), the right factor read from LDS
-    auto chain = [&](const uint4* __restrict__ C) {
+    v4f acc[NR][CB];
+    // acc = C xa (C in chain order, nib input row blocks)
+    auto mul = [&](const uint4* __restrict__ C, auto nib) {
+        constexpr int NIB = decltype(nib)::value;
 #pragma unroll
         for (int i = 0; i < NR; ++i)
-            if (wave + 4 * i < RB) xa[wave + 4 * i][lane] = acc[i];
-        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            const int ob = wave + 4 * i;
-            if (ob < RB) {
-                v4f cc = v4f{0.f, 0.f, 0.f, 0.f};
-                const uint4* Cr = C + size_t(ob) * RB * 64 + lane;
+            for (int cb = 0; cb < CB; ++cb) acc[i][cb] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 10
+        for (int rb = 0; rb < NIB; ++rb) {
+            v4f T[CB];
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) {
-                    const uint4 u = Cr[rb * 64];
-                    const v4f T = xa[rb][lane];
-                    cc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(u.x), T[0], cc, 0, 0, 0);
-                    cc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(u.y), T[1], cc, 0, 0, 0);
-                    cc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(u.z), T[2], cc, 0, 0, 0);
-                    cc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(u.w), T[3], cc, 0, 0, 0);
-                }
-                acc[i] = cc;
+            for (int cb = 0; cb < CB; ++cb) T[cb] = xa[rb][cb][lane];
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const uint4 u = C[(size_t(wave * NR + i) * NIB + rb) * 64 + lane];
+                const float a[4] = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z),
+                                    __uint_as_float(u.w)};
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+                        acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], T[cb][k], acc[i][cb], 0, 0, 0);
             }
         }
+    };
+    using IBc = std::integral_constant<int, IB>;
+    using RBc = std::integral_constant<int, RB>;
+    auto exchange = [&]() {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) xa[wave * NR + i][cb][lane] = acc[i][cb];
         __syncthreads();
     };
-    chain(w1c);
-    chain(vc);
-    if (tgt >= 0) {
-        float* dst = out + size_t(tgt) * NP;
+    if constexpr (KP > 0) {
+        for (int rb = wave; rb < IB; rb += WV)
 #pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            const int rb = wave + 4 * i;
-            if (rb < RB)
-                *reinterpret_cast<float4*>(dst + rb * 16 + g4) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+            for (int cb = 0; cb < CB; ++cb) xa[rb][cb][lane] = load_sum(rb, cb);
+        __syncthreads();
+        mul(qc, IBc{});
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+            if (tgt[cb] >= 0 && xflag[tgt[cb]])
+#pragma unroll
+                for (int i = 0; i < NR; ++i) {
+                    const float4 v = *reinterpret_cast<const float4*>(xpsi + size_t(tgt[cb]) * NP +
+                                                                      (wave * NR + i) * 16 + g4);
+                    acc[i][cb] += v4f{v.x, v.y, v.z, v.w};
+                }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[i][cb] = load_sum(wave * NR + i, cb);
+    }
+    if (DOWN && l2l) {
+        float d[CB][3];
+        if constexpr (STK)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                d[cb][0] = d[cb][1] = d[cb][2] = 0.f;
+                if (par[cb] >= 0) centre_diff(geo, anchor[par[cb]], anchor[tgt[cb]], d[cb]);
+            }
+        const uint4* A = l2l + (size_t(o) * KC * RB + wave * NR) * 128 + lane;
+#pragma unroll (NR == 1 ? 5 : 1)
+        for (int kc = 0; kc < KC; ++kc) {
+            float b[CB][8];
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                const size_t at = size_t(par[cb] >= 0 ? par[cb] : 0) * NP + kc * 32 + g8;
+                load8(b[cb], phi + at);   // (box 0's where there is no parent)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) b[cb][k] = par[cb] >= 0 ? b[cb][k] : 0.f;
+                if constexpr (STK) {
+                    float bx[8], by[8], bz[8];
+                    load8(bx, par[cb] >= 0 ? s0 + at : nullptr);
+                    load8(by, par[cb] >= 0 ? s1 + at : nullptr);
+                    load8(bz, par[cb] >= 0 ? s2 + at : nullptr);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) b[cb][k] += d[cb][0] * bx[k] + d[cb][1] * by[k] + d[cb][2] * bz[k];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const uint4 u0 = A[(kc * RB + i) * 128], u1 = A[(kc * RB + i) * 128 + 64];
+                const float a[8] = {__uint_as_float(u0.x), __uint_as_float(u0.y), __uint_as_float(u0.z),
+                                    __uint_as_float(u0.w), __uint_as_float(u1.x), __uint_as_float(u1.y),
+                                    __uint_as_float(u1.z), __uint_as_float(u1.w)};
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+                        acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[cb][k], acc[i][cb], 0, 0, 0);
+            }
         }
     }
+    exchange();
+    mul(w1c, RBc{});
+    exchange();
+    mul(vc, RBc{});
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+        if (tgt[cb] >= 0)
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+                *reinterpret_cast<float4*>(phi + size_t(tgt[cb]) * NP + (wave * NR + i) * 16 + g4) =
+                    make_float4(acc[i][cb][0], acc[i][cb][1], acc[i][cb][2], acc[i][cb][3]);
+}
+
+// ------------------------------------------------------------------ M2M
+// psi_u(box) = sum over its children o of M2M[o] phi_u(child), for the
+// non-leaf boxes nonleaf[nl_start .. + nl_count) of one level; the
+// check-to-equivalent map follows in k_c2e.  Apart from the map, a level's
+// output row blocks are independent and spread over the chip.
+// A wave owns NR row blocks by CB column blocks of 16 boxes and adds the
+// octants in order.  At few boxes (NR = CB = 1) the launch is one chain of 8 KC
+// dependent steps, so the fragments and source values of G steps (five at
+// p = 6 and 8) are read at once.  At many it is bound by FP32 MFMA
+// issue and the reads of operators and sources from L2.
+// STK: the children's columns are moved into the box's frame, as in k_c2e.
+template <int NP, int NR, int CB, bool STK>
+__global__ __launch_bounds__(256, 2) void k_m2m(int nblk, int nl_start, int nl_count, const int* __restrict__ nonleaf,
+                                             const int2* __restrict__ child, const float* __restrict__ phi,
+                                             float* __restrict__ psi, const uint4* __restrict__ ops,
+                                             const int4* __restrict__ anchor, BoxGeom geo,
+                                             const float* __restrict__ s0, const float* __restrict__ s1,
+                                             const float* __restrict__ s2) {
+    constexpr int RB = NP / 16, KC = NP / 32, RG = RB / NR;
+    constexpr int G = NR > 1 || STK ? 1 : KC == 10 ? 5 : KC == 7 ? 1 : KC, NG = KC / G;   // chunks per step, steps per octant
+    static_assert(RG * NR == RB && NG * G == KC, "whole row and chunk groups");
+    __builtin_amdgcn_s_setprio(2);   // issue ahead of the near-field waves sharing the SIMD
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g4 = 4 * (lane >> 4), g8 = 8 * (lane >> 4);
+    const int job = xcd_remap(blockIdx.x, nblk) * 4 + wave;
+    const int rg = job % RG, grp = job / RG;
+    if (grp * 16 * CB >= nl_count) return;   // whole wave (no barrier in this kernel)
+    int box[CB];
+    int2 ch[CB];
+    int mask = 0;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        const int slot = (grp * CB + cb) * 16 + (lane & 15);
+        box[cb] = slot < nl_count ? nonleaf[nl_start + slot] : -1;
+        ch[cb] = box[cb] >= 0 ? child[box[cb]] : make_int2(0, 0);
+        mask |= ch[cb].y;
+    }
+    int flags = 0;   // the octants any column of the wave has
+#pragma unroll
+    for (int o = 0; o < 8; ++o)
+        if (__ballot((mask >> o) & 1)) flags |= 1 << o;
+    v4f acc[NR][CB];
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[i][cb] = v4f{0.f, 0.f, 0.f, 0.f};
+    struct Step {
+        uint4 a[G][NR][2];
+        float b[CB][G][8];
+    };
+    auto fetch = [&](Step& f, int o, int kg) {
+        const uint4* A = ops + ((size_t(o) * KC + kg * G) * RB + rg * NR) * 128 + lane;
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                f.a[q][i][0] = A[(q * RB + i) * 128];
+                f.a[q][i][1] = A[(q * RB + i) * 128 + 64];
+            }
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            const bool has = (ch[cb].y >> o) & 1;
+            const int sb = has ? ch[cb].x + __popc(ch[cb].y & ((1 << o) - 1)) : 0;
+#pragma unroll
+            for (int q = 0; q < G; ++q) {
+                const size_t at = size_t(sb) * NP + (kg * G + q) * 32 + g8;
+                load8(f.b[cb][q], phi + at);   // (box 0's where there is no child)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) f.b[cb][q][k] = has ? f.b[cb][q][k] : 0.f;
+                if constexpr (STK)
+                    if (has) {
+                        float bx[8], by[8], bz[8], d[3];
+                        centre_diff(geo, anchor[sb], anchor[box[cb]], d);
+                        load8(bx, s0 + at);
+                        load8(by, s1 + at);
+                        load8(bz, s2 + at);
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+                            f.b[cb][q][k] += d[0] * bx[k] + d[1] * by[k] + d[2] * bz[k];
+                    }
+            }
+        }
+    };
+    auto multiply = [&](const Step& f) {
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                const uint4 u0 = f.a[q][i][0], u1 = f.a[q][i][1];
+                const float a[8] = {__uint_as_float(u0.x), __uint_as_float(u0.y), __uint_as_float(u0.z),
+                                    __uint_as_float(u0.w), __uint_as_float(u1.x), __uint_as_float(u1.y),
+                                    __uint_as_float(u1.z), __uint_as_float(u1.w)};
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb)
+                        acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], f.b[cb][q][k], acc[i][cb], 0, 0, 0);
+            }
+    };
+    int left = __popc(flags) * NG;   // steps to multiply
+    int o = flags ? __builtin_ctz(flags) : 8, kg = 0;   // next step to read (o = 8: none)
+    auto next = [&](Step& f) {
+        if (o >= 8) return;
+        fetch(f, o, kg);
+        if (++kg < NG) return;
+        kg = 0;
+        flags &= flags - 1;
+        o = flags ? __builtin_ctz(flags) : 8;
+    };
+    Step f0;
+    if constexpr (G > 1) {
+        for (; left > 0; --left) {
+            next(f0);
+            multiply(f0);
+        }
+    } else {   // one step in flight while one multiplies
+        Step f1;
+        next(f0);
+        while (left > 0) {
+            next(f1);
+            multiply(f0);
+            if (--left == 0) break;
+            next(f0);
+            multiply(f1);
+            --left;
+        }
+    }
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+        if (box[cb] >= 0)
+#pragma unroll
+            for (int i = 0; i < NR; ++i)
+                *reinterpret_cast<float4*>(psi + size_t(box[cb]) * NP + (rg * NR + i) * 16 + g4) =
+                    make_float4(acc[i][cb][0], acc[i][cb][1], acc[i][cb][2], acc[i][cb][3]);
 }
 
 // ------------------------------------------------------------------ leaf evaluation: L2P + M2P
@@ -1204,22 +1240,18 @@ __global__ __launch_bounds__(256) void k_far_grad(const int2* __restrict__ items
 #undef KIFMM_FARG_ITEM
 }
 
-// Compressed M2L change of basis on MFMA, for the boxes [b0, b0 + nb):
-//   out[b][j] = sum_k in[b][k] W[j][k]        (ACCUM: out[b][j] += ...)
-// with W row-major [NOUT][NIN] and `in` the sum of nsplit arrays split_stride
-// apart.  The projection phi_k = Q^T phi_u takes W = Q^T ([kp][NP]); the
-// expansion psi_d += Q (sum of the partial psi_k) takes W = Q ([NP][kp]),
-// adding only to the boxes whose check potentials the P2L kernel wrote
-// (xflag); the others are stored.
+// Compressed M2L: the projection phi_k = Q^T phi_u on MFMA, for the boxes
+// [b0, b0 + nb): out[b][j] = sum_k in[b][k] W[j][k] with W = Q^T row-major
+// [kp][NP].  (The expansion out of the basis is the first factor of the
+// downward check-to-equivalent map.)
 // A wave owns 16 boxes and CPW of the NOUT/16 column tiles (v_mfma_f32_16x16x4_f32,
 // operand layout as in the file header).  In a 16-wide k chunk the lane in
 // group kk = lane/16 loads the float4 k0 + 4 kk .. k0 + 4 kk + 3 of its box row
 // and of the W row of its column, and step s of the four MFMAs takes component
 // s: k = k0 + 4 kk + s, the same permutation on both operands.
-template <int NIN, int NOUT, bool ACCUM>
+template <int NIN, int NOUT>
 __global__ __launch_bounds__(256) void k_basis(int b0, int nb, const float* __restrict__ W,
-                                               const float* __restrict__ in, int nsplit, size_t split_stride,
-                                               float* __restrict__ out, const int* __restrict__ xflag) {
+                                               const float* __restrict__ in, float* __restrict__ out) {
     constexpr int T = NOUT / 16, NCP = T % 2 == 0 ? 2 : 1, CPW = T / NCP;   // column parts, tiles per wave
     static_assert(NIN % 32 == 0 && NOUT % 16 == 0, "tile");
     __builtin_amdgcn_s_setprio(2);   // issue ahead of the near-field waves sharing the SIMD
@@ -1237,13 +1269,10 @@ __global__ __launch_bounds__(256) void k_basis(int b0, int nb, const float* __re
     for (int k0 = 0; k0 < NIN; k0 += 32) {
         // two chunks per step: a box row's 128 contiguous bytes in one go
         float4 a0 = make_float4(0.f, 0.f, 0.f, 0.f), a1 = a0;
-        if (live)
-            for (int sp = 0; sp < nsplit; ++sp) {
-                const float4 x0 = *reinterpret_cast<const float4*>(arow + sp * split_stride + k0);
-                const float4 x1 = *reinterpret_cast<const float4*>(arow + sp * split_stride + k0 + 16);
-                a0.x += x0.x; a0.y += x0.y; a0.z += x0.z; a0.w += x0.w;
-                a1.x += x1.x; a1.y += x1.y; a1.z += x1.z; a1.w += x1.w;
-            }
+        if (live) {
+            a0 = *reinterpret_cast<const float4*>(arow + k0);
+            a1 = *reinterpret_cast<const float4*>(arow + k0 + 16);
+        }
 #pragma unroll
         for (int t = 0; t < CPW; ++t) {
             const float4 w0 = *reinterpret_cast<const float4*>(wrow + size_t(16 * t) * NIN + k0);
@@ -1264,9 +1293,8 @@ __global__ __launch_bounds__(256) void k_basis(int b0, int nb, const float* __re
         const int b = row0 + 4 * kk + v;
         if (b >= end) continue;
         float* o = out + size_t(b) * NOUT + 16 * cp * CPW + i;
-        const bool add = ACCUM && xflag[b];
 #pragma unroll
-        for (int t = 0; t < CPW; ++t) o[16 * t] = add ? o[16 * t] + c[t][v] : c[t][v];
+        for (int t = 0; t < CPW; ++t) o[16 * t] = c[t][v];
     }
 }
 
@@ -1404,40 +1432,92 @@ void launch_m2l(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, const StokesFra
 #undef KIFMM_M2L_TILE
 }
 
-// Compressed M2L: project (phi_k = Q^T phi_u) or expand (psi_d += Q psi_k)
-// the boxes from the first V level on, for right-hand side r.
+// Compressed M2L: project (phi_k = Q^T phi_u) the boxes from the first V
+// level on, for right-hand side r.
 template <int NP, int KP>
-void project_expand_kp(kifmm_plan* P, bool project, int r, hipStream_t s) {
+void project_kp(kifmm_plan* P, int r, hipStream_t s) {
     const int lv = first_v_level(P);
     if (P->depth < lv) return;
     const int b0 = int(P->lev[lv].start), nb = int(P->B) - b0;
     if (nb <= 0) return;
-    const M2LBasis& cm = *P->cm;
-    const size_t sn = size_t(P->B) * NP, sk = size_t(P->B) * KP;
     // work items: 16 boxes by one of the (one or two) column parts, four per block
-    const auto blocks = [&](int nout) {
-        const int parts = (nout / 16) % 2 == 0 ? 2 : 1;
-        return dim3(unsigned(nblk(int64_t(nblk(nb, 16)) * parts, 4)));
-    };
-    if (project)
-        hipLaunchKernelGGL((k_basis<NP, KP, false>), blocks(KP), dim3(256), 0, s, b0, nb, cm.qt.as<float>(),
-                           P->phi_u.as<float>() + r * sn, 1, size_t(0), P->phi_k.as<float>() + r * sk, nullptr);
-    else
-        hipLaunchKernelGGL((k_basis<KP, NP, true>), blocks(NP), dim3(256), 0, s, b0, nb, cm.q.as<float>(),
-                           P->psi_m.as<float>() + r * sk, P->m2l_split_used, 2 * sk, P->psi_d.as<float>() + r * sn,
-                           P->xflag.as<int>());
+    const int parts = (KP / 16) % 2 == 0 ? 2 : 1;
+    hipLaunchKernelGGL((k_basis<NP, KP>), dim3(unsigned(nblk(int64_t(nblk(nb, 16)) * parts, 4))), dim3(256), 0, s, b0,
+                       nb, P->cm->qt.as<float>(), P->phi_u.as<float>() + r * size_t(P->B) * NP,
+                       P->phi_k.as<float>() + r * size_t(P->B) * KP);
 }
 
-template <int NP>
-void project_expand(kifmm_plan* P, bool project, int r, hipStream_t s) {
+// Calls f(integral_constant<KP>) for the compressed tile in use (0 without one).
+template <int NP, class F>
+void with_kp(const kifmm_plan* P, F f) {
+    const int kp = P->cm ? P->cm->kp : 0;
+    if (kp == 0) return f(std::integral_constant<int, 0>{});
     // the basis is only used when its tile is smaller than the surface's
-    const int kp = P->cm->kp;
-    if constexpr (NP > 32) if (kp == 32) return project_expand_kp<NP, 32>(P, project, r, s);
-    if constexpr (NP > 64) if (kp == 64) return project_expand_kp<NP, 64>(P, project, r, s);
-    if constexpr (NP > 128) if (kp == 128) return project_expand_kp<NP, 128>(P, project, r, s);
-    if constexpr (NP > 160) if (kp == 160) return project_expand_kp<NP, 160>(P, project, r, s);
-    if constexpr (NP > 224) if (kp == 224) return project_expand_kp<NP, 224>(P, project, r, s);
+    if constexpr (NP > 32) if (kp == 32) return f(std::integral_constant<int, 32>{});
+    if constexpr (NP > 64) if (kp == 64) return f(std::integral_constant<int, 64>{});
+    if constexpr (NP > 128) if (kp == 128) return f(std::integral_constant<int, 128>{});
+    if constexpr (NP > 160) if (kp == 160) return f(std::integral_constant<int, 160>{});
+    if constexpr (NP > 224) if (kp == 224) return f(std::integral_constant<int, 224>{});
     throw Error(KIFMM_ERR_STATE, "unsupported compressed M2L size");
+}
+
+// Check-to-equivalent map of the boxes list[b0 .. b0+nb) (upward) or of their
+// children (downward).
+template <int NP, int KP, bool DOWN, bool STK>
+void launch_c2e(kifmm_plan* P, const int* list, int64_t b0, int64_t nb, const float* psi, size_t split_stride,
+                const float* xpsi, const uint4* l2l, const uint4* w1c, const uint4* vc, float* phi,
+                const float* const* stk3, hipStream_t s) {
+    if (nb <= 0) return;
+    const BoxGeom geo{{P->lo[0], P->lo[1], P->lo[2]}, P->side};
+    const float* const none[3] = {nullptr, nullptr, nullptr};
+    const float* const* s3 = STK ? stk3 : none;
+    const int boxes = DOWN ? int(8 * nb) : int(nb);
+#define KIFMM_C2E(WIDE, CBV)                                                                                        \
+    do {                                                                                                            \
+        constexpr int WV = chain_waves(NP, WIDE);                                                                   \
+        const int blocks = nblk(nb, 16 * CBV) * (DOWN ? 8 : 1);                                                     \
+        hipLaunchKernelGGL((k_c2e<NP, WV, CBV, KP, DOWN, STK>), dim3(unsigned(blocks)), dim3(64 * WV), 0, s, blocks, \
+                           int(b0), int(nb), list, P->bx_child.as<int2>(), psi, P->m2l_split_used, split_stride,    \
+                           xpsi, P->xflag.as<int>(), KP ? P->cm->q.as<uint4>() : nullptr, l2l, w1c, vc, phi,        \
+                           P->bx_anchor.as<int4>(), geo, s3[0], s3[1], s3[2]);                                      \
+    } while (0)
+    // four column blocks do not fit the registers of the wide or framed forms
+    if (boxes <= kC2eOne) {
+        KIFMM_C2E(true, 1);
+    } else if constexpr (NP == 320 || STK) {
+        KIFMM_C2E(false, 2);
+    } else {
+        if (boxes <= kC2eTwo) KIFMM_C2E(false, 2);
+        else KIFMM_C2E(false, 4);
+    }
+#undef KIFMM_C2E
+}
+
+// M2M into a level's non-leaves.
+template <int NP>
+void launch_m2m(kifmm_plan* P, int level, const uint4* ops, const float* phi, float* psi, const float* const* stk3,
+                hipStream_t s) {
+    const LevelInfo& li = P->lev[level];
+    if (li.nl_count == 0) return;
+    const BoxGeom geo{{P->lo[0], P->lo[1], P->lo[2]}, P->side};
+    constexpr int RB = NP / 16;
+#define KIFMM_M2M(NRV, CBV, STKV, S0, S1, S2)                                                                    \
+    do {                                                                                                         \
+        const int blocks = nblk(int64_t(nblk(li.nl_count, 16 * CBV)) * (RB / NRV), 4);                           \
+        hipLaunchKernelGGL((k_m2m<NP, NRV, CBV, STKV>), dim3(unsigned(blocks)), dim3(256), 0, s, blocks,         \
+                           int(li.nl_start), int(li.nl_count), P->nonleaf.as<int>(), P->bx_child.as<int2>(),     \
+                           phi, psi, ops, P->bx_anchor.as<int4>(), geo, S0, S1, S2);                             \
+    } while (0)
+    const float* const none = nullptr;
+    const bool few = li.nl_count <= kM2mFew;
+    if (stk3) {
+        if (few) KIFMM_M2M(1, 1, true, stk3[0], stk3[1], stk3[2]);
+        else KIFMM_M2M(2, 2, true, stk3[0], stk3[1], stk3[2]);
+    } else {
+        if (few) KIFMM_M2M(1, 1, false, none, none, none);
+        else KIFMM_M2M(2, 2, false, none, none, none);
+    }
+#undef KIFMM_M2M
 }
 
 // One sweep over the tree for the right-hand sides r0 .. r1-1: 0 = the
@@ -1450,7 +1530,6 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
     const Operators& op = *P->ops;
     // right-hand side 1 of a Stokes sweep carries the fourth charge in per-box frames
     auto stk = [&](int r) { return sf != nullptr && r == 1; };
-    const int4* anc = P->bx_anchor.as<int4>();
     const int B = int(P->B);
     const size_t stride = size_t(B) * NP;
     BoxGeom geo{{P->lo[0], P->lo[1], P->lo[2]}, P->side};
@@ -1485,29 +1564,22 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
     if (rec) record_phase(P, 0, s);
     between();
     // upward UC2E of the leaves (every level from ld in one launch), then
-    // M2M + UC2E of the non-leaves, deepest level first; a column block holds
-    // leaves only or non-leaves only, so no leaf waits on the M2M terms of
-    // the children of others
+    // M2M and UC2E of the non-leaves, deepest level first; no leaf waits on the
+    // M2M terms of the children of others
     int64_t lf0 = 0;   // leaves above level ld, at the front of the leaf list
     for (int l = 0; l < ld; ++l) lf0 += P->lev[l].count - P->lev[l].nl_count;
-    const int nlf = int(P->nleaves - lf0);
     for (int r = r0; r < r1; ++r) {
-        auto up = [&](const int* list, int b0, int nb, bool shift) {
-            const int blocks = nblk(nb, 16);
-            if (blocks == 0) return;
-#define KIFMM_UP(STKV, S0, S1, S2)                                                                                 \
-    hipLaunchKernelGGL((k_updown<NP, true, STKV>), dim3(blocks), dim3(WAVES * 64), 0, s, blocks, b0, nb, list, 0, 0, \
-                       0, P->nonleaf.as<int>(), P->bx_child.as<int2>(), P->bx_leaf.as<int>(),                       \
-                       P->psi_u.as<float>() + r * stride, 1, size_t(0), P->phi_u.as<float>() + r * stride,         \
-                       P->phi_u.as<float>() + r * stride, op.m2m.as<uint4>(), op.uc2e_w1.as<uint4>(),               \
-                       op.uc2e_v.as<uint4>(), anc, geo, S0, S1, S2)
-            if (shift) KIFMM_UP(true, sf->up[0], sf->up[1], sf->up[2]);
-            else KIFMM_UP(false, (const float*)nullptr, (const float*)nullptr, (const float*)nullptr);
-#undef KIFMM_UP
+        float* psi = P->psi_u.as<float>() + r * stride;
+        float* phi = P->phi_u.as<float>() + r * stride;
+        const auto c2e = [&](const int* list, int64_t first, int64_t nb) {
+            launch_c2e<NP, 0, false, false>(P, list, first, nb, psi, 0, nullptr, nullptr, op.uc2e_w1.as<uint4>(),
+                                            op.uc2e_v.as<uint4>(), phi, nullptr, s);
         };
-        up(P->leaves.as<int>(), int(lf0), nlf, false);
-        for (int l = depth; l >= ld; --l)
-            up(P->nonleaf.as<int>(), int(P->lev[l].nl_start), int(P->lev[l].nl_count), stk(r));
+        c2e(P->leaves.as<int>(), lf0, P->nleaves - lf0);
+        for (int l = depth; l >= ld; --l) {
+            launch_m2m<NP>(P, l, op.m2m.as<uint4>(), phi, psi, stk(r) ? sf->up : nullptr, s);
+            c2e(P->nonleaf.as<int>(), P->lev[l].nl_start, P->lev[l].nl_count);
+        }
     }
     // periodic root: every image beyond the root's neighbours
     if (P->periodic) {
@@ -1518,7 +1590,10 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
     }
     // compressed M2L: its sources in the common basis
     if (P->cm)
-        for (int r = r0; r < r1; ++r) project_expand<NP>(P, true, r, s);
+        for (int r = r0; r < r1; ++r)
+            with_kp<NP>(P, [&](auto kp) {
+                if constexpr (decltype(kp)::value > 0) project_kp<NP, decltype(kp)::value>(P, r, s);
+            });
     if (rec) record_phase(P, 1, s);
     // downward check potentials of the boxes the P2L kernel sums (flagged in
     // xflag; the M2L and the compressed expansion read no other box's value
@@ -1540,29 +1615,25 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
         for (int r = r0; r < r1; ++r) launch_m2l<NP>(P, 1, r, s);
     }
     if (rec) record_phase(P, 3, s);
-    // compressed M2L: its results back on the check surfaces, added to the X
-    // list (timed with the downward pass)
-    if (P->cm)
-        for (int r = r0; r < r1; ++r) project_expand<NP>(P, false, r, s);
-    // L2L + DC2E, coarse to fine
+    // L2L + DC2E, coarse to fine; the check potentials: the M2L partials (with
+    // the X list in the first) or, compressed, their sum expanded out of the
+    // basis, plus the X list
     for (int r = r0; r < r1; ++r)
         for (int l = first_v_level(P); l <= depth; ++l) {
             const LevelInfo& pl = P->lev[l - 1];
-            const int blocks = nblk(pl.nl_count, 16) * 8;
-            if (blocks == 0) continue;
-#define KIFMM_DOWN(STKV, S0, S1, S2)                                                                              \
-    hipLaunchKernelGGL((k_updown<NP, false, STKV>), dim3(blocks), dim3(WAVES * 64), 0, s, blocks, 0, 0,           \
-                       (const int*)nullptr, int(pl.nl_start), int(pl.nl_count), l > ld ? 1 : 0,                    \
-                       P->nonleaf.as<int>(), P->bx_child.as<int2>(), P->bx_leaf.as<int>(),                         \
-                       P->cm ? P->psi_d.as<float>() + r * stride : P->psi_m.as<float>() + r * stride,              \
-                       P->cm ? 1 : P->m2l_split_used, 2 * stride, P->phi_d.as<float>() + r * stride,               \
-                       P->phi_d.as<float>() + r * stride, op.l2l.as<uint4>(), op.dc2e_w1.as<uint4>(),              \
-                       op.dc2e_v.as<uint4>(), anc, geo, S0, S1, S2)
-            // the check potentials: M2L partials (with the X list in the first), or,
-            // compressed, the expanded sum already in psi_d
-            if (stk(r)) KIFMM_DOWN(true, sf->dn[0], sf->dn[1], sf->dn[2]);
-            else KIFMM_DOWN(false, (const float*)nullptr, (const float*)nullptr, (const float*)nullptr);
-#undef KIFMM_DOWN
+            with_kp<NP>(P, [&](auto kp) {
+                constexpr int KP = decltype(kp)::value;
+                const size_t sk = size_t(B) * (KP ? KP : NP);
+                const auto go = [&](auto st) {
+                    launch_c2e<NP, KP, true, decltype(st)::value>(
+                        P, P->nonleaf.as<int>(), pl.nl_start, pl.nl_count, P->psi_m.as<float>() + r * sk, 2 * sk,
+                        P->psi_d.as<float>() + r * stride, l > ld ? op.l2l.as<uint4>() : nullptr,
+                        op.dc2e_w1.as<uint4>(), op.dc2e_v.as<uint4>(), P->phi_d.as<float>() + r * stride,
+                        sf ? sf->dn : nullptr, s);
+                };
+                if (stk(r)) go(std::true_type{});
+                else go(std::false_type{});
+            });
         }
     if (rec) record_phase(P, 4, s);
 }

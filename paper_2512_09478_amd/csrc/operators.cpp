@@ -162,17 +162,17 @@ void frag_bf16(const uint16_t* hi, const uint16_t* lo, int np, uint16_t* out) {
                 }
 }
 
-// Chain order of an np x np operator whose right factor is a result still in
+// Chain order of an np x nk operator whose right factor is a result still in
 // MFMA accumulator layout: output block ob, k block rb, lane l holds
 // A[16 ob + l%16][16 rb + 4 (l/16) .. +3].  One output block is a contiguous
-// chunk of np/16 * 64 16-byte words.
-void frag_chain(const float* A, int np, uint32_t* out) {
-    const int RB = np / 16;
-    for (int ob = 0; ob < RB; ++ob)
+// chunk of nk/16 * 64 16-byte words.
+void frag_chain(const float* A, int np, int nk, uint32_t* out) {
+    const int OB = np / 16, RB = nk / 16;
+    for (int ob = 0; ob < OB; ++ob)
         for (int rb = 0; rb < RB; ++rb)
             for (int l = 0; l < 64; ++l) {
                 size_t w = (size_t(ob) * RB + rb) * 64 + l;
-                memcpy(out + 4 * w, A + size_t(ob * 16 + (l & 15)) * np + rb * 16 + 4 * (l >> 4), 16);
+                memcpy(out + 4 * w, A + size_t(ob * 16 + (l & 15)) * nk + rb * 16 + 4 * (l >> 4), 16);
             }
 }
 
@@ -218,13 +218,13 @@ std::unique_ptr<Operators> build_operators(int p, double tau) {
         }
     {
         std::vector<uint32_t> c(size_t(np) * np);
-        frag_chain(w1u.data(), np, c.data());
+        frag_chain(w1u.data(), np, np, c.data());
         upload(op->uc2e_w1, c.data(), c.size() * 4);
-        frag_chain(vu.data(), np, c.data());
+        frag_chain(vu.data(), np, np, c.data());
         upload(op->uc2e_v, c.data(), c.size() * 4);
-        frag_chain(w1d.data(), np, c.data());
+        frag_chain(w1d.data(), np, np, c.data());
         upload(op->dc2e_w1, c.data(), c.size() * 4);
-        frag_chain(vd.data(), np, c.data());
+        frag_chain(vd.data(), np, np, c.data());
         upload(op->dc2e_v, c.data(), c.size() * 4);
     }
 
@@ -404,7 +404,9 @@ std::unique_ptr<M2LBasis> build_m2l_basis(int p, double rtol) {
             q[size_t(c) * kp + r] = float(U[size_t(c) * n + r]);
             qt[size_t(r) * np + c] = float(U[size_t(c) * n + r]);
         }
-    upload(b->q, q.data(), q.size() * 4);
+    std::vector<uint32_t> qchain(q.size());
+    frag_chain(q.data(), np, kp, qchain.data());
+    upload(b->q, qchain.data(), qchain.size() * 4);
     upload(b->qt, qt.data(), qt.size() * 4);
     // cores Q^T M(d) Q in the M2L kernel's gather-fragment order at kp
     const size_t per = size_t(kp) * kp;
