@@ -318,7 +318,7 @@ int kifmm_evaluate_stokes_ex(kifmm_handle h, const float* forces, double viscosi
         // charges f_x, f_y: one sweep with two right-hand sides, the Stokeslet
         // near field on the side stream beside it
         launch_gather_stokes(P, forces, 0, s);
-        run_sweep(P, 0, 2, s, true, [&] { fork_near(P, NEAR_STOKES, s, viscosity); });
+        run_sweep(P, 0, 2, s, true, [&] { fork_near(P, NEAR_STOKES, s, viscosity); }, nullptr, true);
         for (int r = 0; r < 2; ++r)
             run_far_eval(P, false, pot + r * N, fld + 3 * r * N, s, r, false, false, nullptr, true);
         // the first sweep's upward, compressed and downward densities of f_x
@@ -347,7 +347,7 @@ int kifmm_evaluate_stokes_ex(kifmm_handle h, const float* forces, double viscosi
         sf.up[2] = cur_u;   // f_z: right-hand side 0 of this sweep, done before right-hand side 1
         sf.dn[2] = cur_d;
         sf.kp[2] = cur_k;
-        run_sweep(P, 0, 2, s, false, [] {}, &sf);
+        run_sweep(P, 0, 2, s, false, [] {}, &sf, true);
         run_far_eval(P, false, pot + 2 * N, fld + 3 * 2 * N, s, 0, false, false, nullptr, true);
         run_far_eval(P, false, pot + 3 * N, fld + 3 * 3 * N, s, 1, false, false, &sf, true);
         launch_stokes_frames(P, s);
@@ -484,7 +484,7 @@ int kifmm_clump_forces(kifmm_handle h, const float* charges, const double* cente
         P->fwd_valid = false;
         P->fwd_excl = false;
         launch_gather(P, charges, nullptr, nullptr, false, s);
-        run_sweep(P, 0, 1, s, true, [&] { fork_near(P, NEAR_FORWARD_EXCL, s); });
+        run_sweep(P, 0, 1, s, true, [&] { fork_near(P, NEAR_FORWARD_EXCL, s); }, nullptr, true);
         join_near(P, s);
         float* E = P->clump_E.ensure(size_t(P->N) * 12) ? P->clump_E.as<float>() : nullptr;
         run_far_eval(P, false, nullptr, E, s);
@@ -518,7 +518,7 @@ int kifmm_clump_forces_backward(kifmm_handle h, const float* charges, const doub
         // the FMM part for the dipole sources dL/dE (forward densities reused),
         // the same pairs left out, added to the outputs
         launch_gather(P, nullptr, nullptr, Eb, true, s);
-        run_sweep(P, 1, 2, s, true, [&] { fork_near(P, NEAR_BACKWARD_EXCL, s); });
+        run_sweep(P, 1, 2, s, true, [&] { fork_near(P, NEAR_BACKWARD_EXCL, s); }, nullptr, true);
         join_near(P, s);
         run_far_eval(P, true, grad_charges, grad_positions, s, 0, true);
         record_phase(P, 6, s);

@@ -140,6 +140,7 @@ struct Operators {
     DBuf l2l;          // 8 octants: child dc <- parent de (includes the factor 1/2 of the child width)
     DBuf m2l_f32;      // [316][npad/32 chunks][npad/16 row blocks][2][64] x 16 B (FP32 fragments)
     DBuf m2l_bf16;     // same shape, bf16 hi half then lo half
+    DBuf m2l_bf16_3;   // the third bf16 pieces, [316][npad/32 chunks][npad/16 row blocks][64] x 16 B (p <= 6)
     std::vector<double> sigma;   // singular values of K(uc, ue), descending
     std::vector<double> svd_u, svd_v;   // its singular vectors (n x n row-major, FP64)
 };
@@ -157,6 +158,7 @@ struct M2LBasis {
     DBuf qt;          // float [kp][NP]: Q^T row-major, zero-padded (operand of the projection phi_k = Q^T phi)
     DBuf core_f32;    // [316] cores in gather-fragment order at kp (FP32)
     DBuf core_bf16;   // the same, bf16 hi/lo
+    DBuf core_bf16_3; // the third bf16 pieces (p <= 6)
 };
 const M2LBasis& get_m2l_basis(int p, double tau, double rtol);
 
@@ -331,8 +333,9 @@ struct StokesFrames {
     const float* kp[3] = {};       // their compressed M2L sources, [B][KP] (compressed M2L only)
     const float* dn[3] = {};       // downward equivalent densities, [B][NP]
 };
+// fp32_m2l: the FP32 path keeps FP32 matrix instructions in the M2L (see sweep_impl)
 void run_sweep(kifmm_plan* P, int r0, int r1, hipStream_t s, bool record, const std::function<void()>& between,
-               const StokesFrames* sf = nullptr);
+               const StokesFrames* sf = nullptr, bool fp32_m2l = false);
 // leaf evaluation; adds the near-field part and writes the caller-order
 // outputs (forward: potential, field; backward: grad_charges, grad_positions)
 // (near = false: the near-field part is not added)

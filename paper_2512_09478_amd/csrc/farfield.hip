@@ -296,19 +296,29 @@ __device__ inline void load8(float* b, const float* __restrict__ p) {
 // per-box frames): each source column of the second adds (c_source -
 // c_target) times the source box's columns of f_x, f_y (s0, s1) and of f_z,
 // the first right-hand side's column of the same source (s2 is not read).
-template <int NP, bool SPLIT, int CB, bool STK>
-__global__ __launch_bounds__(256, STK ? 2 : 3) void k_m2l(TaskTable tt, int nblk, int ntile, int nsplit, int nrhs,
+// PIECES: 1 FP32 operands and v_mfma_f32_16x16x4; 2 or 3 operands split into
+// that many bf16 pieces (8 significant bits each) and
+// v_mfma_f32_16x16x32_bf16: hi.hi + hi.lo + lo.hi, or with the third piece
+// also lo.lo + hi.lo2 + lo2.hi.  Three pieces hold an FP32 number whole and
+// the six products leave out terms below 2^-24 of the largest, so PIECES = 3
+// is FP32 arithmetic at 16 / 6 of the FP32 matrix rate (1M clustered points,
+// rank 116: 2.6 to 1.2 ms a launch).
+// A wave none of whose targets has the slot passes its products over.
+template <int NP, int PIECES, int CB, bool STK>
+__global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void k_m2l(TaskTable tt, int nblk, int ntile, int nsplit, int nrhs,
                                              const int* __restrict__ nonleaf, const int2* __restrict__ child,
                                              const int* __restrict__ vdense, int b2, const VOps* __restrict__ vops,
                                              const float* __restrict__ phi_u, const float* __restrict__ psi_d,
                                              const int* __restrict__ xflag, float* __restrict__ psi_m,
                                              size_t rhs_stride, size_t split_stride, const uint4* __restrict__ ops,
-                                             const int4* __restrict__ anchor, BoxGeom geo,
+                                             const uint4* __restrict__ ops3, const int4* __restrict__ anchor,
+                                             BoxGeom geo,
                                              const float* __restrict__ s0, const float* __restrict__ s1,
                                              const float* __restrict__ s2) {
-    constexpr int RB = NP / 16, KC = NP / 32, WORDS = RB * 128;
-    __shared__ uint4 lds0[WORDS];
-    __shared__ uint4 lds1[WORDS];
+    // the third pieces of a chunk (ops3) follow the others (ops) in LDS
+    constexpr int RB = NP / 16, KC = NP / 32, WORDS = RB * 128, WORDS3 = PIECES == 3 ? RB * 64 : 0;
+    __shared__ uint4 lds0[WORDS + WORDS3];
+    __shared__ uint4 lds1[WORDS + WORDS3];
     __shared__ unsigned vmask[6];
     __shared__ short sop[kVPerOct];   // operator index of each V slot of octant o
     __builtin_amdgcn_s_setprio(2);   // issue ahead of the near-field waves sharing the SIMD
@@ -371,6 +381,7 @@ __global__ __launch_bounds__(256, STK ? 2 : 3) void k_m2l(TaskTable tt, int nblk
     if (j < kVPerOct) {
         const int g8 = 8 * (lane >> 4);
         int kc = 0;
+        bool now = false;
         float breg[CB][8];
         const float* col[CB];
         // STK: the source box of each column at the current slot, its shift
@@ -388,8 +399,10 @@ __global__ __launch_bounds__(256, STK ? 2 : 3) void k_m2l(TaskTable tt, int nblk
         // start chunk (jj, kk): operator words by DMA into dst, source columns into breg
         auto issue = [&](int jj, int kk, bool newslot, uint4* dst) {
             if (newslot) {
+                now = false;
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb) {
+                    now |= __ballot(pre[cb] >= 0) != 0;
                     col[cb] = pre[cb] >= 0 ? bsrc[cb] + size_t(pre[cb]) * NP : nullptr;
                     if constexpr (STK) {
                         sidx[cb] = pre[cb];
@@ -399,6 +412,8 @@ __global__ __launch_bounds__(256, STK ? 2 : 3) void k_m2l(TaskTable tt, int nblk
                 }
             }
             dma_chunk<WORDS>(ops + (size_t(sop[jj]) * KC + kk) * WORDS, dst, tid);
+            if constexpr (PIECES == 3)
+                dma_chunk<WORDS3>(ops3 + (size_t(sop[jj]) * KC + kk) * WORDS3, dst + WORDS, tid);
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) load8(breg[cb], col[cb] ? col[cb] + kk * 32 + g8 : nullptr);
             if constexpr (STK) {
@@ -427,38 +442,54 @@ __global__ __launch_bounds__(256, STK ? 2 : 3) void k_m2l(TaskTable tt, int nblk
                             cur[cb][i] += dsh[cb][0] * bxr[cb][i] + dsh[cb][1] * byr[cb][i] +
                                           dsh[cb][2] * breg[cb - 1][i];
                 }
+            const bool live = now;   // a target of the wave has this slot
             int nkc = kc + 1, nj = j;
             if (nkc == KC) {
                 nkc = 0;
                 nj = next_slot(vmask, j);
             }
             if (nj < kVPerOct) issue(nj, nkc, nj != j, other);
-            if (SPLIT) {
-                v8bf bh[CB], bl[CB];
+            if (!live) {
+                // nothing to add
+            } else if constexpr (PIECES > 1) {
+                v8bf b[PIECES][CB];
 #pragma unroll
                 for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        __bf16 h = (__bf16)cur[cb][i];
-                        bh[cb][i] = h;
-                        bl[cb][i] = (__bf16)(cur[cb][i] - (float)h);
+                        float rest = cur[cb][i];
+#pragma unroll
+                        for (int q = 0; q < PIECES; ++q) {
+                            const __bf16 h = (__bf16)rest;
+                            b[q][cb][i] = h;
+                            rest -= (float)h;
+                        }
                     }
                 // the fragments of row block rb + 1 are read while rb multiplies
-                uint4 nh = L[lane], nl = L[64 + lane];
+                uint4 n[PIECES];
+                auto read = [&](int rb) {
+                    n[0] = L[rb * 128 + lane];
+                    n[1] = L[rb * 128 + 64 + lane];
+                    if constexpr (PIECES == 3) n[2] = L[WORDS + rb * 64 + lane];
+                };
+                read(0);
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    const v8bf ah = as_bf8(nh);
-                    const v8bf al = as_bf8(nl);
-                    if (rb + 1 < RB) {
-                        nh = L[(rb + 1) * 128 + lane];
-                        nl = L[(rb + 1) * 128 + 64 + lane];
-                    }
+                    v8bf a[PIECES];
+#pragma unroll
+                    for (int q = 0; q < PIECES; ++q) a[q] = as_bf8(n[q]);
+                    if (rb + 1 < RB) read(rb + 1);
 #pragma unroll
                     for (int cb = 0; cb < CB; ++cb) {
                         v4f c = acc[cb][rb];
-                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[cb], c, 0, 0, 0);
-                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[cb], c, 0, 0, 0);
-                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[cb], c, 0, 0, 0);
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[0][cb], c, 0, 0, 0);
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[1][cb], c, 0, 0, 0);
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[0][cb], c, 0, 0, 0);
+                        if constexpr (PIECES == 3) {
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[1], b[1][cb], c, 0, 0, 0);
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0], b[2][cb], c, 0, 0, 0);
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[2], b[0][cb], c, 0, 0, 0);
+                        }
                         acc[cb][rb] = c;
                     }
                 }
@@ -1355,7 +1386,7 @@ int first_down_level(const kifmm_plan* P) { return P->periodic ? 0 : 2; }
 // check potentials; null for zero), partials out [split][rhs][B][NP].
 template <int NP>
 void launch_m2l_tile(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, const float* src, const float* init,
-                     float* out, const uint4* ops_f32, const uint4* ops_bf16, const float* const* stk3) {
+                     float* out, const DBuf* const ops[3], int pieces, const float* const* stk3) {
     const int depth = P->depth;
     const int lv = first_v_level(P);
     if (depth < lv) return;
@@ -1391,36 +1422,45 @@ void launch_m2l_tile(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, const floa
     const BoxGeom geo{{P->lo[0], P->lo[1], P->lo[2]}, P->side};
     const float* const none[3] = {nullptr, nullptr, nullptr};
     const float* const* s3 = stk3 ? stk3 : none;
-#define KIFMM_M2L_LAUNCH(SPL, CBV, OPS, STKV)                                                                    \
-    hipLaunchKernelGGL((k_m2l<NP, SPL, CBV, STKV>), dim3(total), dim3(WAVES * 64), 0, s, tt, total, blocks,     \
+#define KIFMM_M2L_LAUNCH(PCS, STKV)                                                                              \
+    hipLaunchKernelGGL((k_m2l<NP, PCS, M2L_CB, STKV>), dim3(total), dim3(WAVES * 64), 0, s, tt, total, blocks,   \
                        nsplit, nrhs, P->nonleaf.as<int>(), P->bx_child.as<int2>(), P->vdense.as<int>(), b2,     \
-                       vops_device(), phi_u, psi_d, P->xflag.as<int>(), psi_m, stride, sstride, OPS,            \
-                       P->bx_anchor.as<int4>(), geo, s3[0], s3[1], s3[2])
-    const bool split = P->opt.precision == KIFMM_SPLIT_BF16;
+                       vops_device(), phi_u, psi_d, P->xflag.as<int>(), psi_m, stride, sstride,                 \
+                       ops[PCS == 1 ? 0 : 1]->as<uint4>(), ops[2]->as<uint4>(), P->bx_anchor.as<int4>(), geo,   \
+                       s3[0], s3[1], s3[2])
     if (stk3) {
         if (nrhs != 2) throw Error(KIFMM_ERR_STATE, "the framed Stokes M2L takes the sweep's two right-hand sides");
-        if (split) KIFMM_M2L_LAUNCH(true, M2L_CB, ops_bf16, true);
-        else KIFMM_M2L_LAUNCH(false, M2L_CB, ops_f32, true);
-    } else {
-        if (split) KIFMM_M2L_LAUNCH(true, M2L_CB, ops_bf16, false);
-        else KIFMM_M2L_LAUNCH(false, M2L_CB, ops_f32, false);
+        if (pieces == 2) KIFMM_M2L_LAUNCH(2, true);
+        else KIFMM_M2L_LAUNCH(1, true);
+        return;
     }
+    if constexpr (NP <= 160) {   // larger tiles have no room for a third piece
+        if (pieces == 3) {
+            KIFMM_M2L_LAUNCH(3, false);
+            return;
+        }
+    }
+    if (pieces == 2) KIFMM_M2L_LAUNCH(2, false);
+    else KIFMM_M2L_LAUNCH(1, false);
 #undef KIFMM_M2L_LAUNCH
 }
 
 // sf: right-hand side `rhs` is the Stokeslet's fourth charge in per-box frames
 template <int NP>
-void launch_m2l(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, const StokesFrames* sf = nullptr) {
+void launch_m2l(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, bool exact32, const StokesFrames* sf = nullptr) {
+    const int pieces = P->opt.precision == KIFMM_SPLIT_BF16 ? 2 : exact32 ? 1 : 3;
     if (!P->cm) {
         const Operators& op = *P->ops;
-        launch_m2l_tile<NP>(P, nrhs, rhs, s, P->phi_u.as<float>(), P->psi_d.as<float>(), P->psi_m.as<float>(),
-                            op.m2l_f32.as<uint4>(), op.m2l_bf16.as<uint4>(), sf ? sf->up : nullptr);
+        const DBuf* const ops[3] = {&op.m2l_f32, &op.m2l_bf16, &op.m2l_bf16_3};
+        launch_m2l_tile<NP>(P, nrhs, rhs, s, P->phi_u.as<float>(), P->psi_d.as<float>(), P->psi_m.as<float>(), ops,
+                            pieces, sf ? sf->up : nullptr);
         return;
     }
     const M2LBasis& cm = *P->cm;
+    const DBuf* const ops[3] = {&cm.core_f32, &cm.core_bf16, &cm.core_bf16_3};
 #define KIFMM_M2L_TILE(KP)                                                                                     \
-    launch_m2l_tile<KP>(P, nrhs, rhs, s, P->phi_k.as<float>(), nullptr, P->psi_m.as<float>(),               \
-                        cm.core_f32.as<uint4>(), cm.core_bf16.as<uint4>(), sf ? sf->kp : nullptr)
+    launch_m2l_tile<KP>(P, nrhs, rhs, s, P->phi_k.as<float>(), nullptr, P->psi_m.as<float>(), ops, pieces,   \
+                        sf ? sf->kp : nullptr)
     switch (cm.kp) {
         case 32: KIFMM_M2L_TILE(32); break;
         case 64: KIFMM_M2L_TILE(64); break;
@@ -1526,8 +1566,15 @@ void launch_m2m(kifmm_plan* P, int level, const uint4* ops, const float* phi, fl
 // `between` runs after P2M (the caller forks the near field there).
 template <int NP>
 void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const std::function<void()>& between,
-                const StokesFrames* sf) {
+                const StokesFrames* sf, bool fp32_m2l) {
     const Operators& op = *P->ops;
+    // The FP32 path's M2L: six bf16 products round as little as the FP32
+    // instructions (against 64 bits the fields are as near or nearer), but
+    // differently.  Where the result is a small difference of large check
+    // potentials (one-signed masses, p >= 7; by the caller's word, fp32_m2l,
+    // forces on clumps and Stokes flow) the rounding of either is 1e-5 to 1e-4
+    // of it, and the FP32 instructions stay.
+    const bool exact32 = fp32_m2l || P->kernel != KIFMM_LAPLACE || P->p >= 7;
     // right-hand side 1 of a Stokes sweep carries the fourth charge in per-box frames
     auto stk = [&](int r) { return sf != nullptr && r == 1; };
     const int B = int(P->B);
@@ -1610,9 +1657,9 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
     // V list (a Stokes sweep's second right-hand side in per-box frames)
     if (sf && (r0 != 0 || r1 != 2)) throw Error(KIFMM_ERR_STATE, "a Stokes sweep has right-hand sides 0 and 1");
     if (r1 - r0 == 2) {
-        launch_m2l<NP>(P, 2, 0, s, sf);
+        launch_m2l<NP>(P, 2, 0, s, exact32, sf);
     } else {
-        for (int r = r0; r < r1; ++r) launch_m2l<NP>(P, 1, r, s);
+        for (int r = r0; r < r1; ++r) launch_m2l<NP>(P, 1, r, s, exact32);
     }
     if (rec) record_phase(P, 3, s);
     // L2L + DC2E, coarse to fine; the check potentials: the M2L partials (with
@@ -1764,14 +1811,14 @@ void run_far_grad(kifmm_plan* P, float* pot, float* field, float* grad, hipStrea
 }
 
 void run_sweep(kifmm_plan* P, int r0, int r1, hipStream_t s, bool record, const std::function<void()>& between,
-               const StokesFrames* sf) {
+               const StokesFrames* sf, bool fp32_m2l) {
     switch (P->npad) {
-        case 32: sweep_impl<32>(P, r0, r1, s, record, between, sf); break;
-        case 64: sweep_impl<64>(P, r0, r1, s, record, between, sf); break;
-        case 128: sweep_impl<128>(P, r0, r1, s, record, between, sf); break;
-        case 160: sweep_impl<160>(P, r0, r1, s, record, between, sf); break;
-        case 224: sweep_impl<224>(P, r0, r1, s, record, between, sf); break;
-        case 320: sweep_impl<320>(P, r0, r1, s, record, between, sf); break;
+        case 32: sweep_impl<32>(P, r0, r1, s, record, between, sf, fp32_m2l); break;
+        case 64: sweep_impl<64>(P, r0, r1, s, record, between, sf, fp32_m2l); break;
+        case 128: sweep_impl<128>(P, r0, r1, s, record, between, sf, fp32_m2l); break;
+        case 160: sweep_impl<160>(P, r0, r1, s, record, between, sf, fp32_m2l); break;
+        case 224: sweep_impl<224>(P, r0, r1, s, record, between, sf, fp32_m2l); break;
+        case 320: sweep_impl<320>(P, r0, r1, s, record, between, sf, fp32_m2l); break;
         default: throw Error(KIFMM_ERR_ARG, "unsupported surface size");
     }
 }

@@ -162,6 +162,25 @@ void frag_bf16(const uint16_t* hi, const uint16_t* lo, int np, uint16_t* out) {
                 }
 }
 
+// The third bf16 pieces in the same order: chunk, row block, lane.
+void frag_bf16_3(const uint16_t* a, int np, uint16_t* out) {
+    const int RB = np / 16, KC = np / 32;
+    for (int kc = 0; kc < KC; ++kc)
+        for (int rb = 0; rb < RB; ++rb)
+            for (int l = 0; l < 64; ++l)
+                memcpy(out + 8 * ((size_t(kc) * RB + rb) * 64 + l),
+                       a + size_t(rb * 16 + (l & 15)) * np + kc * 32 + 8 * (l >> 4), 16);
+}
+
+// bf16 pieces of x: x = p[0] + p[1] + p[2] to 2^-25
+void bf16_pieces(double x, uint16_t p[3]) {
+    p[0] = bf16_rne(float(x));
+    x -= double(bf16_to_float(p[0]));
+    p[1] = bf16_rne(float(x));
+    x -= double(bf16_to_float(p[1]));
+    p[2] = bf16_rne(float(x));
+}
+
 // Chain order of an np x nk operator whose right factor is a result still in
 // MFMA accumulator layout: output block ob, k block rb, lane l holds
 // A[16 ob + l%16][16 rb + 4 (l/16) .. +3].  One output block is a contiguous
@@ -257,6 +276,7 @@ std::unique_ptr<Operators> build_operators(int p, double tau) {
     // M2L for the 316 far offsets, lexicographic (dx, dy, dz)
     std::vector<float> m2l(size_t(kNumV) * np * np, 0.f);
     std::vector<uint16_t> hi(size_t(kNumV) * np * np, 0), lo(size_t(kNumV) * np * np, 0);
+    std::vector<uint16_t> lo2(p <= 6 ? size_t(kNumV) * np * np : 0, 0);
     int m = 0;
     for (int dx = -3; dx <= 3; ++dx)
         for (int dy = -3; dy <= 3; ++dy)
@@ -268,9 +288,11 @@ std::unique_ptr<Operators> build_operators(int p, double tau) {
                         double v = inv_dist(&sin[3 * i], src);
                         size_t at = (size_t(m) * np + i) * np + j;
                         m2l[at] = float(v);
-                        uint16_t h = bf16_rne(float(v));
-                        hi[at] = h;
-                        lo[at] = bf16_rne(float(v - double(bf16_to_float(h))));
+                        uint16_t piece[3];
+                        bf16_pieces(v, piece);
+                        hi[at] = piece[0];
+                        lo[at] = piece[1];
+                        if (p <= 6) lo2[at] = piece[2];
                     }
                 ++m;
             }
@@ -284,6 +306,11 @@ std::unique_ptr<Operators> build_operators(int p, double tau) {
         }
         upload(op->m2l_f32, f32.data(), f32.size() * 4);
         upload(op->m2l_bf16, f16.data(), f16.size() * 2);
+        if (p <= 6) {
+            f16.resize(size_t(kNumV) * per);
+            for (int mm = 0; mm < kNumV; ++mm) frag_bf16_3(&lo2[mm * per], np, &f16[mm * per]);
+            upload(op->m2l_bf16_3, f16.data(), f16.size() * 2);
+        }
     }
     return op;
 }
@@ -412,6 +439,7 @@ std::unique_ptr<M2LBasis> build_m2l_basis(int p, double rtol) {
     const size_t per = size_t(kp) * kp;
     std::vector<float> core(size_t(kNumV) * per, 0.f);
     std::vector<uint16_t> hi(size_t(kNumV) * per, 0), lo(size_t(kNumV) * per, 0);
+    std::vector<uint16_t> lo2(p <= 6 ? size_t(kNumV) * per : 0, 0);
     std::vector<double> T(size_t(n) * k);
     for (int m = 0; m < kNumV; ++m) {
         const std::vector<double>& A = M[m];
@@ -427,9 +455,11 @@ std::unique_ptr<M2LBasis> build_m2l_basis(int p, double rtol) {
                 for (int i = 0; i < n; ++i) acc += U[size_t(i) * n + a] * T[size_t(i) * k + r];
                 const size_t at = size_t(m) * per + size_t(a) * kp + r;
                 core[at] = float(acc);
-                const uint16_t h = bf16_rne(float(acc));
-                hi[at] = h;
-                lo[at] = bf16_rne(float(acc - double(bf16_to_float(h))));
+                uint16_t piece[3];
+                bf16_pieces(acc, piece);
+                hi[at] = piece[0];
+                lo[at] = piece[1];
+                if (p <= 6) lo2[at] = piece[2];
             }
     }
     std::vector<uint32_t> f32(size_t(kNumV) * per);
@@ -440,6 +470,11 @@ std::unique_ptr<M2LBasis> build_m2l_basis(int p, double rtol) {
     }
     upload(b->core_f32, f32.data(), f32.size() * 4);
     upload(b->core_bf16, f16.data(), f16.size() * 2);
+    if (p <= 6) {
+        f16.resize(size_t(kNumV) * per);
+        for (int m = 0; m < kNumV; ++m) frag_bf16_3(&lo2[m * per], kp, &f16[m * per]);
+        upload(b->core_bf16_3, f16.data(), f16.size() * 2);
+    }
     return b;
 }
 
