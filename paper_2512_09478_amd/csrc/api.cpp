@@ -103,20 +103,26 @@ enum NearKind { NEAR_FORWARD, NEAR_BACKWARD, NEAR_DIPOLES, NEAR_GRAD, NEAR_GRAD_
 // The near field does not depend on the far-field sweep: it runs on the side
 // stream, forked from `s` after P2M (so that the sweep's first kernel is not
 // queued behind it) and joined back before the leaf evaluation, which adds it
-// to the far field.
-void fork_near(kifmm_plan* P, NearKind kind, hipStream_t s, double viscosity = 1.0) {
+// to the far field.  Neither does P2L (`first`), which goes ahead of it there:
+// on the caller's stream it added 50 to 90 us between the upward pass and the
+// M2L.
+void fork_near(kifmm_plan* P, NearKind kind, hipStream_t s, const std::function<void(hipStream_t)>& first,
+               double viscosity = 1.0) {
     P->nearq.make();
     hipStream_t t = P->nearq.s;
     KIFMM_HIP(hipEventRecord(P->nearq.fork, s));
     KIFMM_HIP(hipStreamWaitEvent(t, P->nearq.fork, 0));
     const bool prof = P->opt.profile && P->events.made;
     if (prof) KIFMM_HIP(hipEventRecord(P->events.p2p[P->events.cur][0], t));
+    first(t);
+    KIFMM_HIP(hipEventRecord(P->nearq.mid, t));
+    if (prof) KIFMM_HIP(hipEventRecord(P->events.p2p[P->events.cur][1], t));
     if (kind == NEAR_BACKWARD || kind == NEAR_BACKWARD_EXCL) launch_p2p_backward(P, t, kind == NEAR_BACKWARD_EXCL);
     else if (kind == NEAR_DIPOLES) launch_p2p_dipoles(P, t);
     else if (kind == NEAR_STOKES) launch_p2p_stokes(P, viscosity, t);
     else if (kind == NEAR_GRAD || kind == NEAR_GRAD_DIPOLES) launch_p2p_gradient(P, kind == NEAR_GRAD_DIPOLES, t);
     else launch_p2p_forward(P, t, kind == NEAR_FORWARD_EXCL);
-    if (prof) KIFMM_HIP(hipEventRecord(P->events.p2p[P->events.cur][1], t));
+    if (prof) KIFMM_HIP(hipEventRecord(P->events.p2p[P->events.cur][2], t));
     KIFMM_HIP(hipEventRecord(P->nearq.join, t));
 }
 
@@ -238,7 +244,7 @@ int kifmm_evaluate(kifmm_handle h, const float* charges, float* potential, float
         P->fwd_valid = false;
         P->fwd_excl = false;
         launch_gather(P, charges, nullptr, nullptr, false, s);
-        run_sweep(P, 0, 1, s, true, [&] { fork_near(P, NEAR_FORWARD, s); });
+        run_sweep(P, 0, 1, s, true, [&](auto& first) { fork_near(P, NEAR_FORWARD, s, first); });
         join_near(P, s);
         run_far_eval(P, false, potential, field, s);
         record_phase(P, 6, s);
@@ -262,7 +268,7 @@ int kifmm_evaluate_dipoles(kifmm_handle h, const float* charges, const float* di
         P->fwd_valid = false;
         P->fwd_excl = false;
         launch_gather(P, charges, charges, dipoles, true, s, true);
-        run_sweep(P, 1, 2, s, true, [&] { fork_near(P, NEAR_DIPOLES, s); });
+        run_sweep(P, 1, 2, s, true, [&](auto& first) { fork_near(P, NEAR_DIPOLES, s, first); });
         join_near(P, s);
         run_far_eval(P, false, potential, field, s, 1);
         record_phase(P, 6, s);
@@ -286,7 +292,7 @@ int kifmm_evaluate_gradient(kifmm_handle h, const float* charges, const float* d
         const int rhs = dipoles ? 1 : 0;
         launch_gather(P, charges, charges, dipoles, dipoles != nullptr, s, true);
         run_sweep(P, rhs, rhs + 1, s, true,
-                  [&] { fork_near(P, dipoles ? NEAR_GRAD_DIPOLES : NEAR_GRAD, s); });
+                  [&](auto& first) { fork_near(P, dipoles ? NEAR_GRAD_DIPOLES : NEAR_GRAD, s, first); });
         join_near(P, s);
         run_far_grad(P, potential, field, field_grad, s, rhs);
         record_phase(P, 6, s);
@@ -318,7 +324,7 @@ int kifmm_evaluate_stokes_ex(kifmm_handle h, const float* forces, double viscosi
         // charges f_x, f_y: one sweep with two right-hand sides, the Stokeslet
         // near field on the side stream beside it
         launch_gather_stokes(P, forces, 0, s);
-        run_sweep(P, 0, 2, s, true, [&] { fork_near(P, NEAR_STOKES, s, viscosity); }, nullptr, true);
+        run_sweep(P, 0, 2, s, true, [&](auto& first) { fork_near(P, NEAR_STOKES, s, first, viscosity); }, nullptr, true);
         for (int r = 0; r < 2; ++r)
             run_far_eval(P, false, pot + r * N, fld + 3 * r * N, s, r, false, false, nullptr, true);
         // the first sweep's upward, compressed and downward densities of f_x
@@ -347,7 +353,7 @@ int kifmm_evaluate_stokes_ex(kifmm_handle h, const float* forces, double viscosi
         sf.up[2] = cur_u;   // f_z: right-hand side 0 of this sweep, done before right-hand side 1
         sf.dn[2] = cur_d;
         sf.kp[2] = cur_k;
-        run_sweep(P, 0, 2, s, false, [] {}, &sf, true);
+        run_sweep(P, 0, 2, s, false, nullptr, &sf, true);
         run_far_eval(P, false, pot + 2 * N, fld + 3 * 2 * N, s, 0, false, false, nullptr, true);
         run_far_eval(P, false, pot + 3 * N, fld + 3 * 3 * N, s, 1, false, false, &sf, true);
         launch_stokes_frames(P, s);
@@ -376,7 +382,7 @@ int kifmm_backward(kifmm_handle h, const float* charges, const float* grad_poten
             P->fwd_excl = false;
         }
         launch_gather(P, charges, grad_potential, grad_field, true, s);
-        run_sweep(P, charges ? 0 : 1, 2, s, true, [&] { fork_near(P, NEAR_BACKWARD, s); });
+        run_sweep(P, charges ? 0 : 1, 2, s, true, [&](auto& first) { fork_near(P, NEAR_BACKWARD, s, first); });
         P->fwd_valid = true;
         join_near(P, s);
         run_far_eval(P, true, grad_charges, grad_positions, s);
@@ -484,7 +490,7 @@ int kifmm_clump_forces(kifmm_handle h, const float* charges, const double* cente
         P->fwd_valid = false;
         P->fwd_excl = false;
         launch_gather(P, charges, nullptr, nullptr, false, s);
-        run_sweep(P, 0, 1, s, true, [&] { fork_near(P, NEAR_FORWARD_EXCL, s); }, nullptr, true);
+        run_sweep(P, 0, 1, s, true, [&](auto& first) { fork_near(P, NEAR_FORWARD_EXCL, s, first); }, nullptr, true);
         join_near(P, s);
         float* E = P->clump_E.ensure(size_t(P->N) * 12) ? P->clump_E.as<float>() : nullptr;
         run_far_eval(P, false, nullptr, E, s);
@@ -518,7 +524,7 @@ int kifmm_clump_forces_backward(kifmm_handle h, const float* charges, const doub
         // the FMM part for the dipole sources dL/dE (forward densities reused),
         // the same pairs left out, added to the outputs
         launch_gather(P, nullptr, nullptr, Eb, true, s);
-        run_sweep(P, 1, 2, s, true, [&] { fork_near(P, NEAR_BACKWARD_EXCL, s); }, nullptr, true);
+        run_sweep(P, 1, 2, s, true, [&](auto& first) { fork_near(P, NEAR_BACKWARD_EXCL, s, first); }, nullptr, true);
         join_near(P, s);
         run_far_eval(P, true, grad_charges, grad_positions, s, 0, true);
         record_phase(P, 6, s);
@@ -727,11 +733,12 @@ int kifmm_get_phase_times_at(kifmm_handle h, int back, float* out, int n) {
         if (!pe.valid[k]) return;
         const hipEvent_t* ev = pe.ev[k];
         KIFMM_HIP(hipEventSynchronize(ev[7]));
-        KIFMM_HIP(hipEventSynchronize(pe.p2p[k][1]));
+        KIFMM_HIP(hipEventSynchronize(pe.p2p[k][2]));
         float ms[8] = {};
         for (int i = 0; i < 5; ++i) KIFMM_HIP(hipEventElapsedTime(&ms[i], ev[i], ev[i + 1]));
         KIFMM_HIP(hipEventElapsedTime(&ms[5], ev[6], ev[7]));
-        KIFMM_HIP(hipEventElapsedTime(&ms[6], pe.p2p[k][0], pe.p2p[k][1]));
+        KIFMM_HIP(hipEventElapsedTime(&ms[2], pe.p2p[k][0], pe.p2p[k][1]));
+        KIFMM_HIP(hipEventElapsedTime(&ms[6], pe.p2p[k][1], pe.p2p[k][2]));
         KIFMM_HIP(hipEventElapsedTime(&ms[7], ev[0], ev[7]));
         for (int i = 0; i < std::min(n, 8); ++i) out[i] = ms[i];
         written = std::min(n, 8);

@@ -185,13 +185,14 @@ struct LevelInfo {
 
 // Phase events of the last kRing profiled calls (a ring, so that a caller
 // can read them after a run of calls without synchronising in between): per
-// call ev[0] start, ev[1..5] after P2M, upward, P2L, M2L, downward on the
+// call ev[0] start, ev[1..5] after P2M, upward, (nothing), M2L, downward on the
 // caller's stream, ev[6] after it has joined the near-field stream, ev[7]
-// after the leaf evaluation; p2p[0..1] around the near field on the side stream.
+// after the leaf evaluation; on the side stream p2p[0] before the P2L and
+// p2p[1..2] around the near field.
 struct PhaseEvents {
     static constexpr int kRing = 64;
     hipEvent_t ev[kRing][8] = {};
-    hipEvent_t p2p[kRing][2] = {};
+    hipEvent_t p2p[kRing][3] = {};
     bool valid[kRing] = {};   // the slot holds a finished call's events
     int cur = kRing - 1;      // slot of the last (or running) call
     int64_t calls = 0;
@@ -202,13 +203,14 @@ struct PhaseEvents {
 // caller's stream with events (default priority).
 struct SideStream {
     hipStream_t s = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
+    hipEvent_t fork = nullptr, mid = nullptr, join = nullptr;   // mid: what precedes the near field is done
     SideStream() = default;
     SideStream(const SideStream&) = delete;
     SideStream& operator=(const SideStream&) = delete;
     ~SideStream() {
         if (s) (void)hipStreamSynchronize(s);
         if (fork) (void)hipEventDestroy(fork);
+        if (mid) (void)hipEventDestroy(mid);
         if (join) (void)hipEventDestroy(join);
         if (s) (void)hipStreamDestroy(s);
     }
@@ -216,6 +218,7 @@ struct SideStream {
         if (s) return;
         KIFMM_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
         KIFMM_HIP(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
+        KIFMM_HIP(hipEventCreateWithFlags(&mid, hipEventDisableTiming));
         KIFMM_HIP(hipEventCreateWithFlags(&join, hipEventDisableTiming));
     }
 };
@@ -334,7 +337,8 @@ struct StokesFrames {
     const float* dn[3] = {};       // downward equivalent densities, [B][NP]
 };
 // fp32_m2l: the FP32 path keeps FP32 matrix instructions in the M2L (see sweep_impl)
-void run_sweep(kifmm_plan* P, int r0, int r1, hipStream_t s, bool record, const std::function<void()>& between,
+using NearFork = std::function<void(const std::function<void(hipStream_t)>& first)>;
+void run_sweep(kifmm_plan* P, int r0, int r1, hipStream_t s, bool record, const NearFork& between,
                const StokesFrames* sf = nullptr, bool fp32_m2l = false);
 // leaf evaluation; adds the near-field part and writes the caller-order
 // outputs (forward: potential, field; backward: grad_charges, grad_positions)

@@ -136,12 +136,14 @@ __device__ void points_to_surface(float& acc, const float4* __restrict__ pts, co
         __syncthreads();
         if (active) {
             if (!src2) {
+#pragma unroll 8
                 for (int k = slice; k < m; k += 2) {
                     const float4 p = sh[k];
                     const float dx = s.x - p.x, dy = s.y - p.y, dz = s.z - p.z;
                     acc += p.w * __frsqrt_rn(dx * dx + dy * dy + dz * dz);
                 }
             } else {
+#pragma unroll 4
                 for (int k = slice; k < m; k += 2) {
                     const float4 p = sh[k];
                     const float4 a = sh2[k];
@@ -1119,12 +1121,18 @@ __global__ __launch_bounds__(256) void k_moments(int64_t N, const float4* __rest
     if (threadIdx.x < 9) part[size_t(blockIdx.x) * 16 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ void k_moments_sum(const double* __restrict__ part, int nb, double* __restrict__ mom) {
+// One block over the partials, in block order (all of them read into LDS
+// first: read one after the other by the summing threads they took 60 us).
+__global__ __launch_bounds__(256) void k_moments_sum(const double* __restrict__ part, double* __restrict__ mom) {
+    __shared__ double sh[kMomentBlocks][9];
+    for (int k = threadIdx.x; k < kMomentBlocks * 9; k += 256) sh[k / 9][k % 9] = part[size_t(k / 9) * 16 + k % 9];
+    __syncthreads();
     const int q = threadIdx.x;
     if (q >= 16) return;
     double t = 0.0;
     if (q < 9)
-        for (int b = 0; b < nb; ++b) t += part[size_t(b) * 16 + q];
+#pragma unroll 16
+        for (int b = 0; b < kMomentBlocks; ++b) t += sh[b][q];
     mom[q] = t;
 }
 
@@ -1563,9 +1571,11 @@ void launch_m2m(kifmm_plan* P, int level, const uint4* ops, const float* phi, fl
 // One sweep over the tree for the right-hand sides r0 .. r1-1: 0 = the
 // charges (monopoles), 1 = the adjoint sources (monopoles dL/du, dipoles
 // dL/dE).  With both, M2L carries the two columns through each operator load.
-// `between` runs after P2M (the caller forks the near field there).
+// `between` (may be empty) runs after P2M: the caller forks the near field there
+// and launches what it is given at the head of that stream, recording
+// nearq.mid behind it.
 template <int NP>
-void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const std::function<void()>& between,
+void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const NearFork& between,
                 const StokesFrames* sf, bool fp32_m2l) {
     const Operators& op = *P->ops;
     // The FP32 path's M2L: six bf16 products round as little as the FP32
@@ -1590,13 +1600,13 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
             hipLaunchKernelGGL(k_moments, dim3(kMomentBlocks), dim3(256), 0, s, int64_t(P->N), pts,
                                r ? P->src2.as<float4>() : nullptr, P->lo[0] + 0.5 * P->side,
                                P->lo[1] + 0.5 * P->side, P->lo[2] + 0.5 * P->side, P->mom_part.as<double>());
-            hipLaunchKernelGGL(k_moments_sum, dim3(1), dim3(64), 0, s, P->mom_part.as<double>(), kMomentBlocks,
+            hipLaunchKernelGGL(k_moments_sum, dim3(1), dim3(256), 0, s, P->mom_part.as<double>(),
                                P->mom.as<double>() + 16 * r);
         }
     }
     if (depth < ld) {
         if (rec) record_phase(P, 0, s);
-        between();
+        if (between) between([](hipStream_t) {});
         if (rec) for (int k = 1; k < 5; ++k) record_phase(P, k, s);
         return;
     }
@@ -1609,7 +1619,22 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
                            (r && !stk(r)) ? P->src2.as<float4>() : nullptr, stk(r) ? sf->frc : nullptr, surf, op.n,
                            geo, P->psi_u.as<float>() + r * stride);
     if (rec) record_phase(P, 0, s);
-    between();
+    // downward check potentials of the boxes the P2L kernel sums (flagged in
+    // xflag; the M2L and the compressed expansion read no other box's value
+    // before writing it).  They need the points only, so they run on the
+    // near-field stream, ahead of the near field.
+    const auto p2l = [&](hipStream_t t) {
+        for (int r = r0; r < r1; ++r)
+            if (P->n_xboxes > 0)
+                hipLaunchKernelGGL(k_p2l<NP>, dim3(unsigned(P->n_xboxes)), dim3(tpb), 0, t, P->xboxes.as<int>(),
+                                   P->x_off.as<int>(), P->x_idx.as<int>(), P->bx_anchor.as<int4>(),
+                                   P->bx_range.as<int2>(), pts, (r && !stk(r)) ? P->src2.as<float4>() : nullptr,
+                                   stk(r) ? sf->frc : nullptr, surf, op.n, geo,
+                                   P->psi_d.as<float>() + r * stride);
+    };
+    const bool aside = between != nullptr;
+    if (aside) between(p2l);
+    else p2l(s);
     // upward UC2E of the leaves (every level from ld in one launch), then
     // M2M and UC2E of the non-leaves, deepest level first; no leaf waits on the
     // M2M terms of the children of others
@@ -1642,18 +1667,10 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
                 if constexpr (decltype(kp)::value > 0) project_kp<NP, decltype(kp)::value>(P, r, s);
             });
     if (rec) record_phase(P, 1, s);
-    // downward check potentials of the boxes the P2L kernel sums (flagged in
-    // xflag; the M2L and the compressed expansion read no other box's value
-    // before writing it)
-    for (int r = r0; r < r1; ++r) {
-        float* psi_d = P->psi_d.as<float>() + r * stride;
-        if (P->n_xboxes > 0)
-            hipLaunchKernelGGL(k_p2l<NP>, dim3(unsigned(P->n_xboxes)), dim3(tpb), 0, s, P->xboxes.as<int>(),
-                               P->x_off.as<int>(), P->x_idx.as<int>(), P->bx_anchor.as<int4>(),
-                               P->bx_range.as<int2>(), pts, (r && !stk(r)) ? P->src2.as<float4>() : nullptr,
-                               stk(r) ? sf->frc : nullptr, surf, op.n, geo, psi_d);
-    }
     if (rec) record_phase(P, 2, s);
+    // the exact M2L starts from the X-list potentials, the compressed one
+    // leaves them to the downward map
+    if (aside && !P->cm) KIFMM_HIP(hipStreamWaitEvent(s, P->nearq.mid, 0));
     // V list (a Stokes sweep's second right-hand side in per-box frames)
     if (sf && (r0 != 0 || r1 != 2)) throw Error(KIFMM_ERR_STATE, "a Stokes sweep has right-hand sides 0 and 1");
     if (r1 - r0 == 2) {
@@ -1662,6 +1679,7 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const st
         for (int r = r0; r < r1; ++r) launch_m2l<NP>(P, 1, r, s, exact32);
     }
     if (rec) record_phase(P, 3, s);
+    if (aside && P->cm) KIFMM_HIP(hipStreamWaitEvent(s, P->nearq.mid, 0));
     // L2L + DC2E, coarse to fine; the check potentials: the M2L partials (with
     // the X list in the first) or, compressed, their sum expanded out of the
     // basis, plus the X list
@@ -1810,7 +1828,7 @@ void run_far_grad(kifmm_plan* P, float* pot, float* field, float* grad, hipStrea
     }
 }
 
-void run_sweep(kifmm_plan* P, int r0, int r1, hipStream_t s, bool record, const std::function<void()>& between,
+void run_sweep(kifmm_plan* P, int r0, int r1, hipStream_t s, bool record, const NearFork& between,
                const StokesFrames* sf, bool fp32_m2l) {
     switch (P->npad) {
         case 32: sweep_impl<32>(P, r0, r1, s, record, between, sf, fp32_m2l); break;
