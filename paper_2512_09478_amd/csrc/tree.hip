@@ -3,7 +3,7 @@
 // passes use).  All integer work is exact and deterministic:
 //
 //   root cube -> FP64 quantisation to 21-bit cells -> 63-bit Morton keys ->
-//   stable LSD radix sort of (key, index) -> level-by-level split of the
+//   merge sort of (key, index) -> level-by-level split of the
 //   sorted key runs -> colleagues by binary search on per-level box keys ->
 //   V list as a dense table per octant-local offset slot, coarse adjacent
 //   leaves top-down, X lists, and U/W by transposition; every CSR row is
@@ -184,23 +184,6 @@ __global__ void k_check_sorted(const uint64_t* __restrict__ rk, const uint32_t* 
     if (!kv_less(rk[r], rv[r], rk[r + 1], rv[r + 1])) atomicOr(err, 1);
 }
 
-// after a stable sort of D by key: runs of equal keys put in index order
-__global__ void k_fix_ties(const uint64_t* __restrict__ dk, uint32_t* __restrict__ dv, int64_t n) {
-    int64_t i = blockIdx.x * int64_t(TB) + threadIdx.x;
-    if (i >= n || (i > 0 && dk[i - 1] == dk[i])) return;
-    int64_t e = i + 1;
-    while (e < n && dk[e] == dk[i]) ++e;
-    for (int64_t a = i + 1; a < e; ++a) {   // insertion sort of the (short) run
-        const uint32_t t = dv[a];
-        int64_t b = a;
-        while (b > i && dv[b - 1] > t) {
-            dv[b] = dv[b - 1];
-            --b;
-        }
-        dv[b] = t;
-    }
-}
-
 // number of elements of the sorted (k, v)[0, n) before (key, val)
 __device__ inline int64_t rank_in(const uint64_t* __restrict__ k, const uint32_t* __restrict__ v, int64_t n,
                                   uint64_t key, uint32_t val) {
@@ -213,15 +196,20 @@ __device__ inline int64_t rank_in(const uint64_t* __restrict__ k, const uint32_t
     return lo;
 }
 
-// merge: every element of A goes to its index plus its rank in B
-__global__ void k_merge_into(const uint64_t* __restrict__ ak, const uint32_t* __restrict__ av, int64_t na,
-                             const uint64_t* __restrict__ bk, const uint32_t* __restrict__ bv, int64_t nb,
-                             uint64_t* __restrict__ ok, uint32_t* __restrict__ ov) {
+// merge of the sorted R and D: every element goes to its index plus its rank
+// in the other
+__global__ void k_merge(const uint64_t* __restrict__ rk, const uint32_t* __restrict__ rv, int64_t nr,
+                        const uint64_t* __restrict__ dk, const uint32_t* __restrict__ dv, int64_t nd,
+                        uint64_t* __restrict__ ok, uint32_t* __restrict__ ov) {
     int64_t i = blockIdx.x * int64_t(TB) + threadIdx.x;
-    if (i >= na) return;
-    const int64_t p = i + rank_in(bk, bv, nb, ak[i], av[i]);
-    ok[p] = ak[i];
-    ov[p] = av[i];
+    if (i >= nr + nd) return;
+    const bool r = i < nr;
+    if (!r) i -= nr;
+    const uint64_t k = r ? rk[i] : dk[i];
+    const uint32_t v = r ? rv[i] : dv[i];
+    const int64_t p = i + (r ? rank_in(dk, dv, nd, k, v) : rank_in(rk, rv, nr, k, v));
+    ok[p] = k;
+    ov[p] = v;
 }
 
 // ----------------------------------------------------------------- scan
@@ -373,324 +361,151 @@ void exclusive_scan2(kifmm_plan* P, const T* in0, T* out0, T* copy0, int64_t n0,
     exclusive_scan<T>(P, in1, out1, n1, s);
 }
 
-// ----------------------------------------------------------------- radix sort
-constexpr int RS_ITEMS = 16;
-constexpr int RS_WAVE_ITEMS = 64 * RS_ITEMS;   // 1024 keys per wave
-constexpr int RS_TILE = 4 * RS_WAVE_ITEMS;     // 4096 keys per block
+// ----------------------------------------------------------------- sort
+// Sort by (key, value), a total order (the values of one sort are distinct):
+// one launch sorts tiles in LDS, then each launch merges groups of eight runs,
+// every entry finding its place in them by binary search (neighbouring entries
+// of a run search along the same lines).  A sort is a short chain of launches,
+// each bound by its searches' dependent reads: 100,003 points take 67 us (13
+// the tiles, 18 a merge) where eight passes by 8-bit digits, three launches
+// each, took 220.  Merging four runs a launch takes 64 us in five launches,
+// sixteen 73 in three.
+constexpr int SORT_SHIFT = 10, SORT_TILE = 1 << SORT_SHIFT;            // entries of a tile
+constexpr int SORT_WAYS_SHIFT = 3, SORT_WAYS = 1 << SORT_WAYS_SHIFT;   // runs merged by one launch
 
-__global__ void k_rs_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
-                          uint32_t* __restrict__ hist, int nblk) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    int64_t base = blockIdx.x * int64_t(RS_TILE);
-    for (int k = threadIdx.x; k < RS_TILE; k += TB) {
-        int64_t i = base + k;
-        if (i < n) atomicAdd(&h[(keys[i] >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    hist[int64_t(threadIdx.x) * nblk + blockIdx.x] = h[threadIdx.x];
-}
+// one or two sorts of the same size (blockIdx.y): input and output
+struct SortSet {
+    const uint64_t* k[2];
+    const uint32_t* v[2];
+    uint64_t* ko[2];
+    uint32_t* vo[2];
+};
 
-// Stable scatter: wave w owns the contiguous quarter [w*1024, (w+1)*1024) of
-// the block's tile and walks it in 16 rounds of 64 keys; peers with equal
-// digits are found with eight ballots, so ranks follow the input order.
-__global__ __launch_bounds__(256) void k_rs_scatter(const uint64_t* __restrict__ kin,
-                                                    const uint32_t* __restrict__ vin,
-                                                    uint64_t* __restrict__ kout,
-                                                    uint32_t* __restrict__ vout, int64_t n, int shift,
-                                                    const uint32_t* __restrict__ off, int nblk) {
-    __shared__ uint32_t cnt[4][256];
-    __shared__ uint32_t base[4][256];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t b0 = blockIdx.x * int64_t(RS_TILE) + w * int64_t(RS_WAVE_ITEMS);
-    uint64_t k[RS_ITEMS];
-    uint32_t v[RS_ITEMS];
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        int64_t i = b0 + r * 64 + lane;
-        k[r] = i < n ? kin[i] : 0;
-        v[r] = i < n ? vin[i] : 0;
-    }
-    for (int d = threadIdx.x; d < 4 * 256; d += TB) (&cnt[0][0])[d] = 0;
-    __syncthreads();
-    const uint64_t lt = lane_lt_mask();
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        int64_t i = b0 + r * 64 + lane;
-        bool valid = i < n;
-        uint32_t dg = uint32_t(k[r] >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
-        for (int bt = 0; bt < 8; ++bt) {
-            uint64_t m = __ballot((dg >> bt) & 1u);
-            peers &= ((dg >> bt) & 1u) ? m : ~m;
-        }
-        if (valid && (peers & lt) == 0) cnt[w][dg] += uint32_t(__popcll(peers));
+// Tiles of SORT_TILE by doubling runs: every round each thread writes its
+// entry to its index in the merged run.  k/v may equal ko/vo (a block reads and
+// writes its own tile only).
+__global__ __launch_bounds__(SORT_TILE) void k_sort_tile(SortSet a, int64_t n) {
+    __shared__ uint64_t sk[SORT_TILE];
+    __shared__ uint32_t sv[SORT_TILE];
+    const int y = blockIdx.y, p = threadIdx.x;
+    const int64_t base = int64_t(blockIdx.x) << SORT_SHIFT;
+    const int m = int(min(int64_t(SORT_TILE), n - base));
+    uint64_t k = 0;
+    uint32_t v = 0;
+    if (p < m) {
+        sk[p] = k = a.k[y][base + p];
+        sv[p] = v = a.v[y][base + p];
     }
     __syncthreads();
-    {
-        int d = threadIdx.x;
-        uint32_t run = off[int64_t(d) * nblk + blockIdx.x];
-        for (int ww = 0; ww < 4; ++ww) {
-            base[ww][d] = run;
-            run += cnt[ww][d];
+    for (int L = 1; L < m; L *= 2) {   // runs of L, the last one shorter
+        const int s0 = (p & ~(L - 1)) ^ L, len = max(0, min(L, m - s0));   // the other run of the pair
+        int lo = 0;
+        for (int st = L; st > 0; st >>= 1) {
+            const int at = min(s0 + lo + st, SORT_TILE) - 1;
+            const uint64_t kq = sk[at];
+            // (& and |: from && and || the compiler made a branch that lost
+            // the result of the lanes with equal keys)
+            const uint32_t vq = kq == k ? sv[at] : 0u;
+            lo += ((lo + st <= len) & ((kq < k) | ((kq == k) & (vq < v)))) ? st : 0;
+        }
+        __syncthreads();
+        if (p < m) {
+            const int to = (p & ~(2 * L - 1)) + (p & (L - 1)) + lo;
+            sk[to] = k;
+            sv[to] = v;
+        }
+        __syncthreads();
+        if (p < m) {
+            k = sk[p];
+            v = sv[p];
         }
     }
-    __syncthreads();
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        int64_t i = b0 + r * 64 + lane;
-        bool valid = i < n;
-        uint32_t dg = uint32_t(k[r] >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
-        for (int bt = 0; bt < 8; ++bt) {
-            uint64_t m = __ballot((dg >> bt) & 1u);
-            peers &= ((dg >> bt) & 1u) ? m : ~m;
-        }
-        uint32_t pos = 0;
-        if (valid) pos = base[w][dg] + uint32_t(__popcll(peers & lt));
-        __builtin_amdgcn_wave_barrier();
-        if (valid) {
-            kout[pos] = k[r];
-            vout[pos] = v[r];
-            if ((peers & lt) == 0) base[w][dg] += uint32_t(__popcll(peers));
-        }
-        __builtin_amdgcn_wave_barrier();
+    if (p < m) {
+        a.ko[y][base + p] = k;
+        a.vo[y][base + p] = v;
     }
 }
 
-// Keys per wave when n keys are dealt to nw waves in contiguous runs of whole
-// rounds of 64 (at most RS_WAVE_ITEMS): a small sort takes only the rounds
-// it needs, on every wave alike.
-__device__ inline int rs_chunk(int n, int nw) { return ((n + 64 * nw - 1) / (64 * nw)) * 64; }
+// Groups of SORT_WAYS sorted runs of 1 << sh entries (the last group may have
+// fewer, its last run may be shorter) merged into one.
+__global__ __launch_bounds__(TB) void k_sort_merge(SortSet a, int64_t n, int sh) {
+    const int y = blockIdx.y;
+    const int64_t i = blockIdx.x * int64_t(TB) + threadIdx.x, L = int64_t(1) << sh;
+    if (i >= n) return;
+    const int64_t g0 = (i >> (sh + SORT_WAYS_SHIFT)) << (sh + SORT_WAYS_SHIFT);
+    // runs of the group, the same for a wave: it lies in one run
+    const int runs = __builtin_amdgcn_readfirstlane(int(min(int64_t(SORT_WAYS), (n - g0 + L - 1) >> sh)));
+    const uint64_t* ak = a.k[y];
+    const uint32_t* av = a.v[y];
+    const uint64_t key = ak[i];
+    const uint32_t val = av[i];
+    int64_t lo[SORT_WAYS];
+#pragma unroll
+    for (int c = 0; c < SORT_WAYS; ++c) lo[c] = 0;
+    for (int64_t st = L; st > 0; st >>= 1) {
+        // a step of every search: entry lo + st - 1 of each run, read whether
+        // the run reaches it or not, so that the reads are in flight together
+        int64_t at[SORT_WAYS];
+        uint64_t kq[SORT_WAYS];
+        uint32_t vq[SORT_WAYS];
+#pragma unroll
+        for (int c = 0; c < SORT_WAYS; ++c) {
+            at[c] = min(g0 + (int64_t(c) << sh) + lo[c] + st, n) - 1;
+            kq[c] = c < runs ? ak[at[c]] : ~0ull;
+            vq[c] = ~0u;
+        }
+        bool tie = false;
+#pragma unroll
+        for (int c = 0; c < SORT_WAYS; ++c) tie |= kq[c] == key;
+        if (tie) {
+#pragma unroll
+            for (int c = 0; c < SORT_WAYS; ++c)
+                if (c < runs) vq[c] = av[at[c]];
+        }
+#pragma unroll
+        for (int c = 0; c < SORT_WAYS; ++c) {
+            const bool in = lo[c] + st <= min(L, n - (g0 + (int64_t(c) << sh)));
+            lo[c] += (in & ((kq[c] < key) | ((kq[c] == key) & (vq[c] < val)))) ? st : 0;
+        }
+    }
+    // (in its own run the search finds the entry's place there)
+    int64_t to = g0;
+#pragma unroll
+    for (int c = 0; c < SORT_WAYS; ++c) to += lo[c];
+    a.ko[y][to] = key;
+    a.vo[y][to] = val;
+}
 
-// The whole sort of at most RS_TILE keys in one block: each pass ranks the
-// keys as k_rs_scatter does (wave w owns the contiguous run [w*cw, (w+1)*cw),
-// peers by ballots), takes the digit offsets from the block's own counts and
-// scatters into LDS, from where the next pass reloads its run.
-__global__ __launch_bounds__(256) void k_rs_block(uint64_t* __restrict__ keys, uint32_t* __restrict__ vals, int n,
-                                                  int passes) {
-    __shared__ uint64_t sk[RS_TILE];
-    __shared__ uint32_t sv[RS_TILE];
-    __shared__ uint32_t cnt[4][256];
-    __shared__ uint32_t base[4][256];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int cw = rs_chunk(n, 4), nr = cw / 64;
-    const int b0 = w * cw;
-    uint64_t k[RS_ITEMS];
-    uint32_t v[RS_ITEMS];
-#pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int i = b0 + r * 64 + lane;
-        k[r] = (r < nr && i < n) ? keys[i] : 0;
-        v[r] = (r < nr && i < n) ? vals[i] : 0;
+// Sort `sets` (1 or 2) arrays of n pairs in place; kt/vt: scratch of n pairs each.
+void sort_pairs(int sets, uint64_t* const* k, uint32_t* const* v, uint64_t* const* kt, uint32_t* const* vt, int64_t n,
+                hipStream_t s) {
+    if (n <= 1) return;
+    int merges = 0;
+    for (int64_t L = SORT_TILE; L < n; L *= SORT_WAYS) ++merges;
+    bool in_t = merges % 2 != 0;   // the tiles go where the last merge ends in place
+    SortSet a{};
+    for (int y = 0; y < sets; ++y) {
+        a.k[y] = k[y];
+        a.v[y] = v[y];
+        a.ko[y] = in_t ? kt[y] : k[y];
+        a.vo[y] = in_t ? vt[y] : v[y];
     }
-    const uint64_t lt = lane_lt_mask();
-    for (int ps = 0; ps < passes; ++ps) {
-        const int shift = 8 * ps;
-        for (int d = threadIdx.x; d < 4 * 256; d += TB) (&cnt[0][0])[d] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RS_ITEMS; ++r) {
-            if (r < nr) {
-                const bool valid = b0 + r * 64 + lane < n;
-                const uint32_t dg = uint32_t(k[r] >> shift) & 255u;
-                uint64_t peers = __ballot(valid);
-                for (int bt = 0; bt < 8; ++bt) {
-                    const uint64_t m = __ballot((dg >> bt) & 1u);
-                    peers &= ((dg >> bt) & 1u) ? m : ~m;
-                }
-                if (valid && (peers & lt) == 0) cnt[w][dg] += uint32_t(__popcll(peers));
-            }
+    hipLaunchKernelGGL(k_sort_tile, dim3(unsigned(nblocks(n, SORT_TILE)), unsigned(sets)), dim3(SORT_TILE), 0, s, a,
+                       n);
+    for (int m = 0; m < merges; ++m, in_t = !in_t) {
+        for (int y = 0; y < sets; ++y) {
+            a.k[y] = in_t ? kt[y] : k[y];
+            a.v[y] = in_t ? vt[y] : v[y];
+            a.ko[y] = in_t ? k[y] : kt[y];
+            a.vo[y] = in_t ? v[y] : vt[y];
         }
-        __syncthreads();
-        {
-            // digit-major, then wave: base[w][d] = (keys with a smaller digit)
-            // + (keys with digit d in earlier quarters)
-            const int d = threadIdx.x;
-            const uint32_t t = cnt[0][d] + cnt[1][d] + cnt[2][d] + cnt[3][d];
-            uint32_t total;
-            uint32_t run = block_exclusive_scan<uint32_t>(t, &total);
-            for (int ww = 0; ww < 4; ++ww) {
-                base[ww][d] = run;
-                run += cnt[ww][d];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RS_ITEMS; ++r) {
-            if (r < nr) {
-                const bool valid = b0 + r * 64 + lane < n;
-                const uint32_t dg = uint32_t(k[r] >> shift) & 255u;
-                uint64_t peers = __ballot(valid);
-                for (int bt = 0; bt < 8; ++bt) {
-                    const uint64_t m = __ballot((dg >> bt) & 1u);
-                    peers &= ((dg >> bt) & 1u) ? m : ~m;
-                }
-                uint32_t pos = 0;
-                if (valid) pos = base[w][dg] + uint32_t(__popcll(peers & lt));
-                __builtin_amdgcn_wave_barrier();
-                if (valid) {
-                    sk[pos] = k[r];
-                    sv[pos] = v[r];
-                    if ((peers & lt) == 0) base[w][dg] += uint32_t(__popcll(peers));
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RS_ITEMS; ++r) {
-            const int i = b0 + r * 64 + lane;
-            if (r < nr && i < n) {
-                k[r] = sk[i];
-                v[r] = sv[i];
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int i = b0 + r * 64 + lane;
-        if (r < nr && i < n) {
-            keys[i] = k[r];
-            vals[i] = v[r];
-        }
+        hipLaunchKernelGGL(k_sort_merge, dim3(unsigned(nblocks(n)), unsigned(sets)), dim3(TB), 0, s, a, n,
+                           SORT_SHIFT + SORT_WAYS_SHIFT * m);
     }
 }
 
-// The whole sort of at most RS_SMALL keys in one block of RS_SMALL_WAVES
-// waves (one launch): wave w holds the run [w cw, (w + 1) cw) in registers,
-// ranks them as k_rs_scatter does and scatters each pass into the other of two
-// global buffers (keys/vals and ktmp/vtmp), from which the next pass reloads
-// its share; an even number of passes ends in keys/vals.
 constexpr int kItemOrderMin = 1024;   // leaf work items sorted by cost only above this count
-constexpr int RS_SMALL_WAVES = 16;
-constexpr int RS_SMALL = RS_SMALL_WAVES * RS_WAVE_ITEMS;   // 16384 keys
-__global__ __launch_bounds__(RS_SMALL_WAVES * 64) void k_rs_small(uint64_t* __restrict__ keys,
-                                                                  uint32_t* __restrict__ vals,
-                                                                  uint64_t* __restrict__ ktmp,
-                                                                  uint32_t* __restrict__ vtmp, int n, int passes) {
-    __shared__ uint32_t cnt[RS_SMALL_WAVES][256];
-    __shared__ uint32_t scan[256];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, t = threadIdx.x;
-    const int cw = rs_chunk(n, RS_SMALL_WAVES), nr = cw / 64;
-    const int b0 = w * cw;
-    uint64_t k[RS_ITEMS];
-    uint32_t v[RS_ITEMS];
-#pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int i = b0 + r * 64 + lane;
-        k[r] = (r < nr && i < n) ? keys[i] : 0;
-        v[r] = (r < nr && i < n) ? vals[i] : 0;
-    }
-    const uint64_t lt = lane_lt_mask();
-    for (int ps = 0; ps < passes; ++ps) {
-        const int shift = 8 * ps;
-        uint64_t* kout = (ps & 1) ? keys : ktmp;
-        uint32_t* vout = (ps & 1) ? vals : vtmp;
-        for (int d = t; d < RS_SMALL_WAVES * 256; d += RS_SMALL_WAVES * 64) (&cnt[0][0])[d] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RS_ITEMS; ++r) {
-            if (r < nr) {
-                const bool valid = b0 + r * 64 + lane < n;
-                const uint32_t dg = uint32_t(k[r] >> shift) & 255u;
-                uint64_t peers = __ballot(valid);
-                for (int bt = 0; bt < 8; ++bt) {
-                    const uint64_t m = __ballot((dg >> bt) & 1u);
-                    peers &= ((dg >> bt) & 1u) ? m : ~m;
-                }
-                if (valid && (peers & lt) == 0) cnt[w][dg] += uint32_t(__popcll(peers));
-            }
-        }
-        __syncthreads();
-        // exclusive scan over the digits of the totals, then per wave
-        uint32_t tot = 0;
-        if (t < 256)
-            for (int ww = 0; ww < RS_SMALL_WAVES; ++ww) tot += cnt[ww][t];
-        if (t < 256) scan[t] = tot;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const uint32_t a = (t < 256 && t >= off) ? scan[t - off] : 0u;
-            __syncthreads();
-            if (t < 256) scan[t] += a;
-            __syncthreads();
-        }
-        if (t < 256) {
-            uint32_t run = scan[t] - tot;
-            for (int ww = 0; ww < RS_SMALL_WAVES; ++ww) {
-                const uint32_t c = cnt[ww][t];
-                cnt[ww][t] = run;   // becomes the wave's base for digit t
-                run += c;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < RS_ITEMS; ++r) {
-            if (r < nr) {
-                const bool valid = b0 + r * 64 + lane < n;
-                const uint32_t dg = uint32_t(k[r] >> shift) & 255u;
-                uint64_t peers = __ballot(valid);
-                for (int bt = 0; bt < 8; ++bt) {
-                    const uint64_t m = __ballot((dg >> bt) & 1u);
-                    peers &= ((dg >> bt) & 1u) ? m : ~m;
-                }
-                uint32_t pos = 0;
-                if (valid) pos = cnt[w][dg] + uint32_t(__popcll(peers & lt));
-                __builtin_amdgcn_wave_barrier();
-                if (valid) {
-                    kout[pos] = k[r];
-                    vout[pos] = v[r];
-                    if ((peers & lt) == 0) cnt[w][dg] += uint32_t(__popcll(peers));
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        __syncthreads();   // the pass's stores are visible to the whole block
-#pragma unroll
-        for (int r = 0; r < RS_ITEMS; ++r) {
-            const int i = b0 + r * 64 + lane;
-            if (r < nr && i < n) {
-                k[r] = kout[i];
-                v[r] = vout[i];
-            }
-        }
-        __syncthreads();
-    }
-}
-
-void radix_sort(kifmm_plan* P, uint64_t* keys, uint32_t* vals, uint64_t* ktmp, uint32_t* vtmp, int64_t n,
-                int bits, hipStream_t s) {
-    if (n <= 0) return;
-    const bool even = ((bits + 7) / 8) % 2 == 0;
-    // one launch: up to 1,024 keys (or an odd number of passes) four waves
-    // exchanging through LDS, else sixteen waves exchanging through L2
-    if (n <= RS_TILE && (n <= 1024 || !even)) {
-        hipLaunchKernelGGL(k_rs_block, dim3(1), dim3(TB), 0, s, keys, vals, int(n), (bits + 7) / 8);
-        return;
-    }
-    if (n <= RS_SMALL && even) {
-        hipLaunchKernelGGL(k_rs_small, dim3(1), dim3(RS_SMALL_WAVES * 64), 0, s, keys, vals, ktmp, vtmp, int(n),
-                           (bits + 7) / 8);
-        return;
-    }
-    int nblk = int((n + RS_TILE - 1) / RS_TILE);
-    P->tmp_f.ensure(size_t(256) * nblk * 4);
-    uint32_t* hist = P->tmp_f.as<uint32_t>();
-    uint64_t *ka = keys, *kb = ktmp;
-    uint32_t *va = vals, *vb = vtmp;
-    int passes = (bits + 7) / 8;
-    for (int ps = 0; ps < passes; ++ps) {
-        int shift = 8 * ps;
-        hipLaunchKernelGGL(k_rs_hist, dim3(nblk), dim3(TB), 0, s, ka, n, shift, hist, nblk);
-        exclusive_scan<uint32_t>(P, hist, hist, int64_t(256) * nblk, s);
-        hipLaunchKernelGGL(k_rs_scatter, dim3(nblk), dim3(TB), 0, s, ka, va, kb, vb, n, shift, hist, nblk);
-        std::swap(ka, kb);
-        std::swap(va, vb);
-    }
-    if (ka != keys) {
-        KIFMM_HIP(hipMemcpyAsync(keys, ka, n * 8, hipMemcpyDeviceToDevice, s));
-        KIFMM_HIP(hipMemcpyAsync(vals, va, n * 4, hipMemcpyDeviceToDevice, s));
-    }
-}
+constexpr int kResortOne = 4096;      // so many displaced points are sorted whatever their share
 
 // ----------------------------------------------------------------- tree levels
 // For each non-leaf parent at level l: child boundaries in its sorted key run
@@ -1433,7 +1248,7 @@ __global__ __launch_bounds__(256) void k_item_fill(int nl, const int* __restrict
         near_items[2 * size_t(at)] = make_int4(t0, int(nt), n0 + b, nr);
         near_items[2 * size_t(at) + 1] = make_int4(r.y - r.x, staged, 0, 0);
         const unsigned long long cn = nt * src, cf = nt * nfar * 64;
-        // heaviest first: 8-bit keys (one radix pass), descending in log2(cost)
+        // heaviest first: keys descending in log2(cost)
         // in steps of 1/8 (costs within 9 % share a key and keep their order)
         key_near[at] = 0xffull - min(0xffull, (unsigned long long)(log2(double(cn) + 1.0) * 8.0));
         key_far[at] = 0xffull - min(0xffull, (unsigned long long)(log2(double(cf) + 1.0) * 8.0));
@@ -1543,8 +1358,8 @@ static int read_int(kifmm_plan* P, const int* dptr, hipStream_t s) {
 // the displaced subsequence D sorted and merged back into the rest R.  Writes
 // the sorted keys and indices (P->keys, P->tmp_b) and returns true; returns
 // false (nothing written that the full sort needs) when R is not in order or
-// D is more than a quarter of the points (and more than one block sorts at
-// once), for the caller's full sort.
+// D is more than a quarter of the points (and more than kResortOne), for the
+// caller's full sort.
 static bool resort(kifmm_plan* P, double scale, hipStream_t s) {
     const int64_t N = P->N;
     const kifmm_options& o = P->opt;
@@ -1573,19 +1388,10 @@ static bool resort(kifmm_plan* P, double scale, hipStream_t s) {
     int h[2];
     read_ints(P, s, {dpos + N, err}, h);
     const int64_t nd = h[0], nr = N - nd;
-    if (h[1] || (nd > N / 4 && nd > RS_TILE)) return false;
-    if (nd > 0) {
-        // D by key (stable, so equal keys stay in their previous order), then
-        // equal keys by index; the scratch of the full sort is free here
-        radix_sort(P, dk, dv, ka, va, nd, 63, s);
-        hipLaunchKernelGGL(k_fix_ties, dim3(nblocks(nd)), dim3(TB), 0, s, dk, dv, nd);
-    }
-    uint64_t* keys = P->keys.as<uint64_t>();
-    uint32_t* idx = P->tmp_b.as<uint32_t>();
-    if (nr > 0)
-        hipLaunchKernelGGL(k_merge_into, dim3(nblocks(nr)), dim3(TB), 0, s, rk, rv, nr, dk, dv, nd, keys, idx);
-    if (nd > 0)
-        hipLaunchKernelGGL(k_merge_into, dim3(nblocks(nd)), dim3(TB), 0, s, dk, dv, nd, rk, rv, nr, keys, idx);
+    if (h[1] || (nd > N / 4 && nd > kResortOne)) return false;
+    sort_pairs(1, &dk, &dv, &ka, &va, nd, s);   // the scratch of the full sort is free here
+    hipLaunchKernelGGL(k_merge, dim3(nblocks(N)), dim3(TB), 0, s, rk, rv, nr, dk, dv, nd, P->keys.as<uint64_t>(),
+                       P->tmp_b.as<uint32_t>());
     ++P->resort_hits;
     return true;
 }
@@ -1647,7 +1453,9 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     if (!(prev_order && resort(P, scale, s))) {
         hipLaunchKernelGGL(k_keys, dim3(nblocks(N)), dim3(TB), 0, s, P->x64.as<double>(), N, P->lo[0], P->lo[1],
                            P->lo[2], scale, P->side, o.explicit_root, keys, idx, bad);
-        radix_sort(P, keys, idx, P->tmp_c.as<uint64_t>(), P->tmp_d.as<uint32_t>(), N, 63, s);
+        uint64_t* kt = P->tmp_c.as<uint64_t>();
+        uint32_t* vt = P->tmp_d.as<uint32_t>();
+        sort_pairs(1, &keys, &idx, &kt, &vt, N, s);
     }
     P->xs.ensure(size_t(N) * 16);
     P->perm.ensure(size_t(N) * 4);
@@ -1885,16 +1693,14 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     P->n_items = ni;
     // leaf work items, heaviest first
     {
-        P->item_tmp.ensure(size_t(ni) * (32 + 8 + 8 + 8 + 4 + 4 + 4 + 4) + 1024);
+        P->item_tmp.ensure(size_t(ni) * (32 + 8 + 4 * 8 + 4 * 4) + 1024);
         char* base = P->item_tmp.as<char>();
         int4* near_items = reinterpret_cast<int4*>(base);
         int2* items = reinterpret_cast<int2*>(base + size_t(ni) * 32);
         uint64_t* kn = reinterpret_cast<uint64_t*>(base + size_t(ni) * 40);
         uint64_t* kf = kn + ni;
-        uint32_t* idn = reinterpret_cast<uint32_t*>(kf + ni);
+        uint32_t* idn = reinterpret_cast<uint32_t*>(kf + 3 * size_t(ni));
         uint32_t* idf = idn + ni;
-        uint32_t* vtmp = idf + ni;
-        P->tmp_c.ensure(size_t(ni) * 8);
         P->n_runs.grow((size_t(nn) + size_t(B)) * 16, 0, s);
         hipLaunchKernelGGL(k_item_fill, dim3(nblocks(nl, 4)), dim3(TB), 0, s, nl, P->leaves.as<int>(),
                            P->bx_range.as<int2>(), noff, P->n_idx.as<int>(), wfoff, b2, ioff, items,
@@ -1902,8 +1708,11 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
         // a grid this small runs in one round on the chip, where the order
         // of the items does not matter: leaf order (the identity ids)
         if (ni > kItemOrderMin) {
-            radix_sort(P, kn, idn, P->tmp_c.as<uint64_t>(), vtmp, ni, 8, s);
-            radix_sort(P, kf, idf, P->tmp_c.as<uint64_t>(), vtmp, ni, 8, s);
+            uint64_t* const k[2] = {kn, kf};
+            uint64_t* const kt[2] = {kf + ni, kf + 2 * size_t(ni)};
+            uint32_t* const v[2] = {idn, idf};
+            uint32_t* const vt[2] = {idf + ni, idf + 2 * size_t(ni)};
+            sort_pairs(2, k, v, kt, vt, ni, s);
         }
         P->items_near.ensure(size_t(ni) * 32);
         P->items_far.ensure(size_t(ni) * 8);
