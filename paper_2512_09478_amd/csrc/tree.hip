@@ -78,8 +78,9 @@ __global__ void k_bbox(const double* __restrict__ x, int64_t N, double* __restri
 // ----------------------------------------------------------------- keys
 // k_d = clamp(floor((x_d - lo_d) * 2^21 / s), 0, 2^21 - 1): one rounded FP64
 // subtraction and an exact power-of-two scaling, as on the host side of any
-// checker, so the keys are bit-reproducible.
-__global__ void k_keys(const double* __restrict__ x, int64_t N, double lo0, double lo1, double lo2,
+// checker, so the keys are bit-reproducible.  The plan's copy of the positions
+// is written on the way.
+__global__ void k_keys(const double* __restrict__ x, double* __restrict__ copy, int64_t N, double lo0, double lo1, double lo2,
                        double scale, double side, int check_root, uint64_t* __restrict__ keys,
                        uint32_t* __restrict__ idx, int* __restrict__ bad) {
     int64_t i = blockIdx.x * int64_t(TB) + threadIdx.x;
@@ -89,6 +90,7 @@ __global__ void k_keys(const double* __restrict__ x, int64_t N, double lo0, doub
     int b = 0;
     for (int d = 0; d < 3; ++d) {
         double v = x[3 * i + d];
+        copy[3 * i + d] = v;
         if (!isfinite(v)) b = 1;
         if (check_root && (v < lo[d] || v > lo[d] + side)) b = 1;
         double f = floor(__dmul_rn(__dsub_rn(v, lo[d]), scale));
@@ -113,7 +115,7 @@ __device__ inline bool kv_less(uint64_t ka, uint32_t ia, uint64_t kb, uint32_t i
     return ka < kb || (ka == kb && ia < ib);
 }
 
-__global__ void k_keys_prev(const double* __restrict__ x, int64_t N, double lo0, double lo1, double lo2,
+__global__ void k_keys_prev(const double* __restrict__ x, double* __restrict__ copy, int64_t N, double lo0, double lo1, double lo2,
                             double scale, double side, int check_root, const int* __restrict__ prev,
                             uint64_t* __restrict__ keys, uint32_t* __restrict__ idx, int* __restrict__ bad) {
     int64_t i = blockIdx.x * int64_t(TB) + threadIdx.x;
@@ -124,6 +126,7 @@ __global__ void k_keys_prev(const double* __restrict__ x, int64_t N, double lo0,
     int b = 0;
     for (int d = 0; d < 3; ++d) {
         double v = x[3 * j + d];
+        copy[3 * i + d] = x[3 * i + d];
         if (!isfinite(v)) b = 1;
         if (check_root && (v < lo[d] || v > lo[d] + side)) b = 1;
         double f = floor(__dmul_rn(__dsub_rn(v, lo[d]), scale));
@@ -234,7 +237,8 @@ __device__ T block_exclusive_scan(T v, T* total) {
 }
 
 template <class T>
-__global__ void k_scan_tiles(const T* __restrict__ in, T* __restrict__ out, int64_t n, T* __restrict__ sums) {
+__device__ inline void scan_tile_body(const T* __restrict__ in, T* __restrict__ out, int64_t n,
+                                      T* __restrict__ sums) {
     int64_t base = blockIdx.x * int64_t(SCAN_TILE) + threadIdx.x * SCAN_ITEMS;
     T v[SCAN_ITEMS];
     T run = 0;
@@ -249,6 +253,11 @@ __global__ void k_scan_tiles(const T* __restrict__ in, T* __restrict__ out, int6
     for (int k = 0; k < SCAN_ITEMS; ++k)
         if (base + k < n) out[base + k] = v[k] + off;
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+
+template <class T>
+__global__ void k_scan_tiles(const T* __restrict__ in, T* __restrict__ out, int64_t n, T* __restrict__ sums) {
+    scan_tile_body<T>(in, out, n, sums);
 }
 
 template <class T>
@@ -307,15 +316,34 @@ __global__ __launch_bounds__(SCAN_ONE_THREADS) void k_scan_one(const T* __restri
     scan_one_body<T>(in, out, nullptr, n);
 }
 
-// Two independent scans of at most SCAN_ONE values, one block each; the first
-// may also write a copy of its result (out2, nullable).
-template <class T>
-__global__ __launch_bounds__(SCAN_ONE_THREADS) void k_scan_one2(const T* __restrict__ in0, T* __restrict__ out0,
-                                                                T* __restrict__ copy0, int n0,
-                                                                const T* __restrict__ in1, T* __restrict__ out1,
-                                                                int n1) {
-    if (blockIdx.x == 0) scan_one_body<T>(in0, out0, copy0, n0);
-    else scan_one_body<T>(in1, out1, nullptr, n1);
+// Exclusive scans of up to five int arrays of the same length (in may equal
+// out); copy (nullable) receives a copy of the first result.
+struct ScanSet {
+    const int* in[5];
+    int* out[5];
+    int* copy;
+};
+
+__global__ __launch_bounds__(SCAN_ONE_THREADS) void k_scan_one_set(ScanSet a, int n) {
+    const int y = blockIdx.x;
+    scan_one_body<int>(a.in[y], a.out[y], y ? nullptr : a.copy, n);
+}
+
+__global__ void k_scan_tiles_set(ScanSet a, int64_t n, int* __restrict__ sums) {
+    const int y = blockIdx.y;
+    scan_tile_body<int>(a.in[y], a.out[y], n, sums + size_t(y) * gridDim.x);
+}
+
+__global__ void k_scan_add_set(ScanSet a, int64_t n, const int* __restrict__ sums) {
+    const int y = blockIdx.y;
+    int64_t base = blockIdx.x * int64_t(SCAN_TILE) + threadIdx.x * SCAN_ITEMS;
+    const int add = sums[size_t(y) * gridDim.x + blockIdx.x];
+    for (int k = 0; k < SCAN_ITEMS; ++k)
+        if (base + k < n) {
+            const int v = a.out[y][base + k] + add;
+            a.out[y][base + k] = v;
+            if (y == 0 && a.copy) a.copy[base + k] = v;
+        }
 }
 
 // Exclusive scan of n values (in may equal out).  The tile sums of nested
@@ -339,26 +367,26 @@ void exclusive_scan(kifmm_plan* P, const T* in, T* out, int64_t n, hipStream_t s
     }
 }
 
-template <class T>
-__global__ void k_copy_int_t(const T* __restrict__ a, T* __restrict__ b, int64_t n) {
-    const int64_t i = blockIdx.x * int64_t(TB) + threadIdx.x;
-    if (i < n) b[i] = a[i];
-}
-
-// Two exclusive scans (in may equal out), in one launch when both fit one
-// block; copy0 (nullable) receives a copy of the first result; n1 = 0 scans
-// only the first.
-template <class T>
-void exclusive_scan2(kifmm_plan* P, const T* in0, T* out0, T* copy0, int64_t n0, const T* in1, T* out1, int64_t n1,
-                     hipStream_t s) {
-    if (n0 <= SCAN_ONE && n1 <= SCAN_ONE && n0 > 0) {
-        hipLaunchKernelGGL(k_scan_one2<T>, dim3(n1 > 0 ? 2 : 1), dim3(SCAN_ONE_THREADS), 0, s, in0, out0, copy0,
-                           int(n0), in1, out1, int(n1));
+// Scans of `sets` arrays of n values: one launch when an array fits one block,
+// else three for all of them.
+void scan_set(kifmm_plan* P, const ScanSet& a, int sets, int64_t n, hipStream_t s) {
+    if (n <= 0) return;
+    if (n <= SCAN_ONE) {
+        hipLaunchKernelGGL(k_scan_one_set, dim3(unsigned(sets)), dim3(SCAN_ONE_THREADS), 0, s, a, int(n));
         return;
     }
-    exclusive_scan<T>(P, in0, out0, n0, s);
-    if (copy0 && n0 > 0) hipLaunchKernelGGL(k_copy_int_t<T>, dim3(nblocks(n0)), dim3(TB), 0, s, out0, copy0, n0);
-    exclusive_scan<T>(P, in1, out1, n1, s);
+    const int nb = nblocks(n, SCAN_TILE);
+    if (nb > SCAN_ONE) {   // beyond 33 million values
+        for (int y = 0; y < sets; ++y) exclusive_scan<int>(P, a.in[y], a.out[y], n, s);
+        if (a.copy) KIFMM_HIP(hipMemcpyAsync(a.copy, a.out[0], size_t(n) * 4, hipMemcpyDeviceToDevice, s));
+        return;
+    }
+    int* sums = static_cast<int*>(P->scan_tmp.ensure(size_t(sets) * nb * 4));
+    ScanSet t{};
+    for (int y = 0; y < sets; ++y) t.in[y] = t.out[y] = sums + size_t(y) * nb;
+    hipLaunchKernelGGL(k_scan_tiles_set, dim3(unsigned(nb), unsigned(sets)), dim3(TB), 0, s, a, n, sums);
+    hipLaunchKernelGGL(k_scan_one_set, dim3(unsigned(sets)), dim3(SCAN_ONE_THREADS), 0, s, t, nb);
+    hipLaunchKernelGGL(k_scan_add_set, dim3(unsigned(nb), unsigned(sets)), dim3(TB), 0, s, a, n, sums);
 }
 
 // ----------------------------------------------------------------- sort
@@ -570,6 +598,36 @@ __device__ inline unsigned long long split_box(int2 r, int l, const uint64_t* __
     return (unsigned long long)c | ((unsigned long long)nl << 32);
 }
 
+// Eight boxes per wave, lane o of a box's eight finding where octant o begins
+// (four-way search, three reads a step): the same bounds and counts, every lane
+// of the box returns the counts.  One wave a box waits for fewer reads in turn
+// (about 3 us a box), but the one block of k_levels_block then takes a level of
+// many boxes in many rounds: with eight boxes a wave on levels of more than 32
+// it takes 46 us, not 90, for 3,018 boxes and 48, not 119, for 3,471 (in
+// platelets).
+__device__ inline unsigned long long split_eight(bool act, int2 r, int l, const uint64_t* __restrict__ keys,
+                                                 int* __restrict__ out, int leaf_size, int adaptive, int max_depth,
+                                                 int Lu) {
+    const int shift = 3 * (kBits - (l + 1));
+    const int lane = threadIdx.x & 63, o = lane & 7, sh8 = lane & ~7;
+    int lo = r.x, hi = act && o ? r.y : r.x;   // the first index with an octant >= o lies in [lo, hi]
+    auto from = [&](int q) { return int((keys[q] >> shift) & 7ull) >= o; };
+    while (lo < hi) {
+        const int len = hi - lo, q1 = lo + (len >> 2), q2 = lo + (len >> 1), q3 = q2 + (len >> 2);
+        const bool p1 = from(q1), p2 = from(q2), p3 = from(q3);
+        hi = p1 ? q1 : p2 ? q2 : p3 ? q3 : hi;
+        lo = p1 ? lo : p2 ? q1 + 1 : p3 ? q2 + 1 : q3 + 1;
+    }
+    const int next = __shfl_down(lo, 1, 64);
+    const int cnt = act ? (o < 7 ? next : r.y) - lo : 0;
+    if (act) out[o] = lo;
+    if (act && o == 7) out[8] = r.y;
+    const bool leaf = adaptive ? (cnt <= leaf_size || l + 1 == max_depth) : (l + 1 == Lu);
+    const unsigned mh = unsigned(__ballot(cnt > 0) >> sh8) & 0xffu;
+    const unsigned mn = unsigned(__ballot(cnt > 0 && !leaf) >> sh8) & 0xffu;
+    return (unsigned long long)__popc(mh) | ((unsigned long long)__popc(mn) << 32);
+}
+
 __global__ void k_split(const int* __restrict__ front, int nf, int l, const uint64_t* __restrict__ keys,
                         const int2* __restrict__ range, int* __restrict__ bounds /*[nf][9]*/,
                         unsigned long long* __restrict__ cnt, int leaf_size, int adaptive, int max_depth, int Lu) {
@@ -676,8 +734,16 @@ __global__ __launch_bounds__(LB_THREADS) void k_levels_block(
         }
         const int nf = nl_count;
         const int* front = nonleaf + nl_start;
-        // split: one wave per front box
-        for (int f = wave; f < nf; f += nw) {
+        // split: one wave per front box, or eight boxes a wave
+        if (nf > 2 * nw) {
+            for (int f0 = 8 * wave; f0 < nf; f0 += 8 * nw) {
+                const int f = f0 + (lane >> 3);
+                const bool act = f < nf;
+                const unsigned long long c = split_eight(act, act ? range[front[f]] : make_int2(0, 0), l, keys,
+                                                         bounds + 9 * f, leaf_size, adaptive, max_depth, Lu);
+                if (act && (lane & 7) == 0) cnt[f] = c;
+            }
+        } else for (int f = wave; f < nf; f += nw) {
             const unsigned long long c =
                 split_box(range[front[f]], l, keys, lane, bounds + 9 * f, leaf_size, adaptive, max_depth, Lu);
             if (lane == 0) cnt[f] = c;
@@ -783,8 +849,10 @@ __device__ inline int find_box(const uint64_t* __restrict__ mkey, int start, int
 // among the boxes of the same level.  Periodic: the neighbour cell wraps
 // around the root and the entry records the image shift.
 __global__ void k_colleagues(int B, const int4* __restrict__ anchor, const uint64_t* __restrict__ mkey,
-                             LevelTable lt, int periodic, int* __restrict__ coll) {
+                             LevelTable lt, int periodic, int* __restrict__ coll, int* __restrict__ xcnt,
+                             int* __restrict__ ucnt, int* __restrict__ wcnt) {
     const int64_t g = int64_t(blockIdx.x) * TB + threadIdx.x;
+    if (g <= B) xcnt[g] = ucnt[g] = wcnt[g] = 0;   // the X, U and W counts start at zero
     if (g >= int64_t(B) * 27) return;
     const int b = int(g / 27), d = int(g % 27);
     const int4 a = anchor[b];
@@ -1069,18 +1137,41 @@ __device__ inline bool direct_xw(int f, const int* __restrict__ leafflag, const 
 // Near list of leaf b: U(b), then X(b) when b is itself such an F, then the
 // W(b) boxes that are; and the far W list: the other W(b) boxes.  One wave per
 // box, entries copied 64 at a time, the W split kept in order by ballots.
-// mode 0 counts (entry B of both count arrays is the scans' last), mode 1 fills.
+// mode 0 counts (entry B of a count array is the scan's last), mode 1 fills.
+// The leaf list, the X-box list and the work items per leaf go along.
+struct BoxLists {
+    int b2;       // first box with a downward density
+    int* leaf;    // 1 at a leaf; mode 1: leaves before this box
+    int* xflag;   // 1 at a box whose X list the P2L kernel sums
+    int* xbox;    // mode 1: such boxes before this one
+    int* item;    // work items of a leaf (at most 64 targets each)
+    int* leaves;
+    int* xboxes;
+};
+
 __global__ __launch_bounds__(256) void k_near(int B, int n, const int* __restrict__ leafflag,
                                               const int2* __restrict__ range, const int* __restrict__ uoff,
                                               const int* __restrict__ uidx, const int* __restrict__ xoff,
                                               const int* __restrict__ xidx, const int* __restrict__ woff,
                                               const int* __restrict__ widx, int* __restrict__ noff,
                                               int* __restrict__ nidx, int* __restrict__ wfoff,
-                                              int* __restrict__ wfidx, int mode) {
+                                              int* __restrict__ wfidx, BoxLists bl, int mode) {
     const int lane = threadIdx.x & 63, b = blockIdx.x * 4 + int(threadIdx.x >> 6);
-    if (b == B && !mode && lane == 0) noff[B] = wfoff[B] = 0;
+    if (b == B && !mode && lane == 0) noff[B] = wfoff[B] = bl.leaf[B] = bl.xflag[B] = bl.item[B] = 0;
     if (b >= B) return;   // whole wave
-    if (!leafflag[b]) {
+    const bool is_leaf = leafflag[b];
+    if (lane == 0) {
+        if (mode) {
+            if (is_leaf) bl.leaves[bl.leaf[b]] = b;
+            if (bl.xflag[b]) bl.xboxes[bl.xbox[b]] = b;
+        } else {
+            const int2 r = range[b];
+            bl.leaf[b] = is_leaf;
+            bl.xflag[b] = b >= bl.b2 && xoff[b + 1] > xoff[b] && !direct_xw(b, leafflag, range, n);
+            bl.item[b] = is_leaf ? (r.y - r.x + 63) / 64 : 0;
+        }
+    }
+    if (!is_leaf) {
         if (!mode && lane == 0) noff[b] = wfoff[b] = 0;
         return;
     }
@@ -1111,31 +1202,6 @@ __global__ __launch_bounds__(256) void k_near(int B, int n, const int* __restric
         noff[b] = at;
         wfoff[b] = atf;
     }
-}
-
-// Leaves, and boxes that take P2L (an X list, and not summed point to point).
-__global__ void k_flags(int B, const int* __restrict__ leafflag, const int2* __restrict__ range, int n,
-                        const int* __restrict__ xcnt, int b2, int* __restrict__ fl, int* __restrict__ fx) {
-    int b = blockIdx.x * TB + threadIdx.x;
-    if (b == B) fl[B] = fx[B] = 0;   // the scans' last entries
-    if (b >= B) return;
-    fl[b] = leafflag[b];
-    fx[b] = (b >= b2 && xcnt[b + 1] > xcnt[b] && !direct_xw(b, leafflag, range, n)) ? 1 : 0;
-}
-
-__global__ void k_zero3(int n, int* __restrict__ a, int* __restrict__ b, int* __restrict__ c) {
-    const int i = blockIdx.x * TB + threadIdx.x;
-    if (i < n) a[i] = b[i] = c[i] = 0;
-}
-
-__global__ void k_compact2(int B, const int* __restrict__ flag0, const int* __restrict__ off0, int* __restrict__ out0,
-                           const int* __restrict__ flag1, const int* __restrict__ off1, int* __restrict__ out1) {
-    int b = blockIdx.x * TB + threadIdx.x;
-    if (b >= B) return;
-    const int* flag = blockIdx.y ? flag1 : flag0;
-    const int* off = blockIdx.y ? off1 : off0;
-    int* out = blockIdx.y ? out1 : out0;
-    if (flag[b]) out[off[b]] = b;
 }
 
 // Counts: V pairs, P2P point pairs (self pairs included), from the lists.
@@ -1169,21 +1235,6 @@ __global__ void k_counts(int B, const int* __restrict__ leafflag, const int2* __
         }
     }
     if (pp) atomicAdd(&out[1], pp);
-}
-
-// Leaf work items of at most 64 targets, with cost estimates for ordering
-// the near-field and leaf-evaluation launches heaviest first.
-__global__ void k_item_count(int B, const int* __restrict__ nl_dev, const int* __restrict__ leaves,
-                             const int2* __restrict__ range, int* __restrict__ cnt) {
-    // entries nl .. B are zero, so that a scan of B + 1 entries ends with the total
-    const int i = blockIdx.x * TB + threadIdx.x;
-    if (i > B) return;
-    if (i >= *nl_dev) {
-        cnt[i] = 0;
-        return;
-    }
-    const int2 r = range[leaves[i]];
-    cnt[i] = (r.y - r.x + 63) / 64;
 }
 
 // One wave per leaf: its near list as runs of contiguous sorted points, then
@@ -1242,7 +1293,7 @@ __global__ __launch_bounds__(256) void k_item_fill(int nl, const int* __restrict
     const unsigned long long nfar = (b >= b2 ? 1 : 0) + (woff[b + 1] - woff[b]);
     const int nitem = (r.y - r.x + 63) / 64;
     for (int c = lane; c < nitem; c += 64) {
-        const int at = off[i] + c, t0 = r.x + 64 * c;
+        const int at = off[b] + c, t0 = r.x + 64 * c;
         const unsigned long long nt = min(64, r.y - t0);
         items[at] = make_int2(b, t0);
         near_items[2 * size_t(at)] = make_int4(t0, int(nt), n0 + b, nr);
@@ -1318,7 +1369,7 @@ void v_slot_offset(int o, int j, int d[3]) {
     for (int k = 0; k < 3; ++k) d[k] = 2 * (Dv[k] - 1) + ((oc >> (2 - k)) & 1) - ((o >> (2 - k)) & 1);
 }
 
-// Read device ints through the plan's pinned words (one copy each, one wait).
+// Device ints to read back.
 struct IntPicks {
     const int* p[8];
     int n;
@@ -1328,8 +1379,8 @@ __global__ void k_pick_ints(IntPicks a, int* __restrict__ out) {
     if (int(threadIdx.x) < a.n) out[threadIdx.x] = *a.p[threadIdx.x];
 }
 
-// Read up to eight device ints: gathered into one staging word array by a
-// one-wave kernel, then one copy and one synchronisation.
+// Read up to eight device ints: a one-wave kernel writes them to the plan's
+// pinned words, then one synchronisation.
 static void read_ints(kifmm_plan* P, hipStream_t s, std::initializer_list<const int*> src, int* dst) {
     int* h = reinterpret_cast<int*>(P->host.get());
     IntPicks a{};
@@ -1337,21 +1388,9 @@ static void read_ints(kifmm_plan* P, hipStream_t s, std::initializer_list<const 
         if (a.n == 8) throw Error(KIFMM_ERR_STATE, "too many values in one read-back");
         a.p[a.n++] = d;
     }
-    if (a.n == 1) {
-        KIFMM_HIP(hipMemcpyAsync(h, a.p[0], 4, hipMemcpyDeviceToHost, s));
-    } else {
-        P->readback.ensure(64);
-        hipLaunchKernelGGL(k_pick_ints, dim3(1), dim3(64), 0, s, a, P->readback.as<int>());
-        KIFMM_HIP(hipMemcpyAsync(h, P->readback.as<int>(), size_t(a.n) * 4, hipMemcpyDeviceToHost, s));
-    }
+    hipLaunchKernelGGL(k_pick_ints, dim3(1), dim3(64), 0, s, a, h);
     KIFMM_HIP(hipStreamSynchronize(s));
     for (int i = 0; i < a.n; ++i) dst[i] = h[i];
-}
-
-static int read_int(kifmm_plan* P, const int* dptr, hipStream_t s) {
-    int v = 0;
-    read_ints(P, s, {dptr}, &v);
-    return v;
 }
 
 // Re-sort from the order of the previous build (same N): keys in that order,
@@ -1360,7 +1399,7 @@ static int read_int(kifmm_plan* P, const int* dptr, hipStream_t s) {
 // false (nothing written that the full sort needs) when R is not in order or
 // D is more than a quarter of the points (and more than kResortOne), for the
 // caller's full sort.
-static bool resort(kifmm_plan* P, double scale, hipStream_t s) {
+static bool resort(kifmm_plan* P, const double* positions, double scale, hipStream_t s) {
     const int64_t N = P->N;
     const kifmm_options& o = P->opt;
     ++P->resort_steps;
@@ -1379,8 +1418,8 @@ static bool resort(kifmm_plan* P, double scale, hipStream_t s) {
     uint64_t* ka = P->tmp_c.as<uint64_t>();
     uint32_t* va = P->tmp_d.as<uint32_t>();
     int* bad = P->flag.as<int>();
-    hipLaunchKernelGGL(k_keys_prev, dim3(nblocks(N)), dim3(TB), 0, s, P->x64.as<double>(), N, P->lo[0], P->lo[1],
-                       P->lo[2], scale, P->side, o.explicit_root, P->perm.as<int>(), ka, va, bad);
+    hipLaunchKernelGGL(k_keys_prev, dim3(nblocks(N)), dim3(TB), 0, s, positions, P->x64.as<double>(), N, P->lo[0],
+                       P->lo[1], P->lo[2], scale, P->side, o.explicit_root, P->perm.as<int>(), ka, va, bad);
     hipLaunchKernelGGL(k_displaced, dim3(nblocks(N + 1)), dim3(TB), 0, s, ka, va, N, flag, err);
     exclusive_scan<int>(P, flag, dpos, N + 1, s);
     hipLaunchKernelGGL(k_split_dr, dim3(nblocks(N)), dim3(TB), 0, s, ka, va, N, flag, dpos, dk, dv, rk, rv);
@@ -1399,9 +1438,7 @@ static bool resort(kifmm_plan* P, double scale, hipStream_t s) {
 void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     const int64_t N = P->N;
     const kifmm_options& o = P->opt;
-    // positions copy
-    P->x64.ensure(size_t(N) * 24);
-    KIFMM_HIP(hipMemcpyAsync(P->x64.p, positions, size_t(N) * 24, hipMemcpyDeviceToDevice, s));
+    P->x64.ensure(size_t(N) * 24);   // copy of the positions, written with the keys
     P->flag.ensure(64);
     int* bad = P->flag.as<int>();
     KIFMM_HIP(hipMemsetAsync(bad, 0, 64, s));
@@ -1413,7 +1450,7 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     } else {
         int nb = std::min<int64_t>(1024, (N + TB - 1) / TB);
         P->tmp_a.ensure(size_t(nb) * 6 * 8);
-        hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(TB), 0, s, P->x64.as<double>(), N, P->tmp_a.as<double>(), bad);
+        hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(TB), 0, s, positions, N, P->tmp_a.as<double>(), bad);
         std::vector<double> part(size_t(nb) * 6);
         int hbad = 0;
         KIFMM_HIP(hipMemcpyAsync(part.data(), P->tmp_a.p, part.size() * 8, hipMemcpyDeviceToHost, s));
@@ -1450,9 +1487,9 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     const bool prev_order = P->sorted_valid;
     P->sorted_valid = false;
     ++P->builds;
-    if (!(prev_order && resort(P, scale, s))) {
-        hipLaunchKernelGGL(k_keys, dim3(nblocks(N)), dim3(TB), 0, s, P->x64.as<double>(), N, P->lo[0], P->lo[1],
-                           P->lo[2], scale, P->side, o.explicit_root, keys, idx, bad);
+    if (!(prev_order && resort(P, positions, scale, s))) {
+        hipLaunchKernelGGL(k_keys, dim3(nblocks(N)), dim3(TB), 0, s, positions, P->x64.as<double>(), N, P->lo[0],
+                           P->lo[1], P->lo[2], scale, P->side, o.explicit_root, keys, idx, bad);
         uint64_t* kt = P->tmp_c.as<uint64_t>();
         uint32_t* vt = P->tmp_d.as<uint32_t>();
         sort_pairs(1, &keys, &idx, &kt, &vt, N, s);
@@ -1495,23 +1532,23 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     bool levels_done = false;
     if (small_tree) {
         const int ncap = int(cap);
-        P->tmp_a.ensure(size_t(ncap) * 9 * 4 + size_t(ncap + 1) * 16 + size_t(kMaxLevels + 1) * 16 + 256);
+        P->tmp_a.ensure(size_t(ncap) * 9 * 4 + size_t(ncap + 1) * 16 + 256);
         char* base = P->tmp_a.as<char>();
         int* bounds = reinterpret_cast<int*>(base);
         unsigned long long* cnt = reinterpret_cast<unsigned long long*>(base + ((size_t(ncap) * 9 * 4 + 15) & ~size_t(15)));
         unsigned long long* offs = cnt + (ncap + 1);
-        int4* levt = reinterpret_cast<int4*>(offs + (ncap + 1));
-        int* levn = reinterpret_cast<int*>(levt + (kMaxLevels + 1));
+        // the level table and, right after it, the two counters go straight to
+        // the plan's pinned words
+        static_assert((kMaxLevels + 1) * 16 + 8 <= 512, "host words");
+        int* hw = reinterpret_cast<int*>(P->host.get());
+        int4* levt = reinterpret_cast<int4*>(hw);
+        int* levn = hw + 4 * (kMaxLevels + 1);
         hipLaunchKernelGGL(k_levels_block, dim3(1), dim3(LB_THREADS), 0, s, keys, ncap, ncap, bounds, cnt, offs,
                            P->bx_anchor.as<int4>(), P->bx_range.as<int2>(), P->bx_parent.as<int>(),
                            P->bx_child.as<int2>(), P->bx_leaf.as<int>(), P->bx_mkey.as<uint64_t>(),
                            P->nonleaf.as<int>(), levt, levn, P->leaf, o.adaptive, o.max_depth, Lu, 1, int(N));
-        // the level table and, right after it, the two counters in one copy
-        static_assert((kMaxLevels + 1) * 16 + 8 <= 512, "host words");
-        int* hw = reinterpret_cast<int*>(P->host.get());
-        KIFMM_HIP(hipMemcpyAsync(hw, levt, size_t(kMaxLevels + 1) * 16 + 8, hipMemcpyDeviceToHost, s));
         KIFMM_HIP(hipStreamSynchronize(s));
-        const int* hn = hw + 4 * (kMaxLevels + 1);
+        const int* hn = levn;
         if (hn[1] == 0) {
             const int nlev = hn[0];
             P->lev.clear();
@@ -1581,8 +1618,14 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     }
     // colleagues
     P->coll.ensure(size_t(B) * 27 * 4);
+    P->x_off.ensure(size_t(B + 1) * 4);
+    int* xoff = P->x_off.as<int>();
+    P->u_off.ensure(size_t(B + 1) * 4);
+    int* uoff = P->u_off.as<int>();
+    P->w_off.ensure(size_t(B + 1) * 4);
+    int* woff = P->w_off.as<int>();
     hipLaunchKernelGGL(k_colleagues, dim3(nblocks(int64_t(B) * 27)), dim3(TB), 0, s, B, P->bx_anchor.as<int4>(),
-                       P->bx_mkey.as<uint64_t>(), lt, P->periodic ? 1 : 0, P->coll.as<int>());
+                       P->bx_mkey.as<uint64_t>(), lt, P->periodic ? 1 : 0, P->coll.as<int>(), xoff, uoff, woff);
     // V dense table
     static DBuf* vt_dev = nullptr;   // per process, small
     if (!vt_dev) {
@@ -1603,16 +1646,8 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
                            int(P->lev[l].count), P->bx_anchor.as<int4>(), P->bx_parent.as<int>(),
                            P->bx_leaf.as<int>(), P->coll.as<int>(), P->cal.as<int>(), bad);
     // X lists (rows over all boxes; non-empty from the first far-field level)
-    P->x_off.ensure(size_t(B + 1) * 4);
-    int* xoff = P->x_off.as<int>();
-    P->u_off.ensure(size_t(B + 1) * 4);
-    int* uoff = P->u_off.as<int>();
     P->tmp_e.ensure(size_t(B + 1) * 4);
     int* cursor = P->tmp_e.as<int>();
-    P->w_off.ensure(size_t(B + 1) * 4);
-    int* woff = P->w_off.as<int>();
-    // the X, U and W counts start at zero: one launch for the three
-    hipLaunchKernelGGL(k_zero3, dim3(nblocks(B + 1)), dim3(TB), 0, s, B + 1, xoff, uoff, woff);
     // List storage is sized by bounds, so that no size is read back here:
     // X(b) <= 26 leaf colleagues of the parent + 26 coarse adjacent leaves of
     // the parent; U(b) <= 27 + 26 of its own, and the finer part adds one
@@ -1630,11 +1665,11 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     // (one launch when small), the X entries with the own part of U, then the
     // finer part of U with the W counts (which read the X entries)
     hipLaunchKernelGGL(k_list_counts, dim3(nbx + 2 * nbu), dim3(TB), 0, s, la, nbx, nbu);
-    exclusive_scan2<int>(P, xoff, xoff, nullptr, B + 1, uoff, uoff, B + 1, s);
+    scan_set(P, ScanSet{{xoff, uoff}, {xoff, uoff}, nullptr}, 2, B + 1, s);
     hipLaunchKernelGGL(k_list_fill_a, dim3(nbx + nbu), dim3(TB), 0, s, la, nbx);
     hipLaunchKernelGGL(k_list_fill_b, dim3(nbu + nbx), dim3(TB), 0, s, la, nbu);
     // W = X transposed: the scan also leaves the cursor (a copy of the offsets)
-    exclusive_scan2<int>(P, woff, woff, cursor, B + 1, nullptr, nullptr, 0, s);
+    scan_set(P, ScanSet{{woff}, {woff}, cursor}, 1, B + 1, s);
     if (nvb > 0) hipLaunchKernelGGL(k_list_fill_w, dim3(nbx), dim3(TB), 0, s, la);
     // every row of X, U and W ascending (U and W were filled through atomics)
     hipLaunchKernelGGL(k_sort_rows, dim3(B, 3), dim3(64), 0, s, B, xoff, P->x_idx.as<int>(), uoff,
@@ -1645,41 +1680,28 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     P->wf_off.ensure(size_t(B + 1) * 4);
     int* noff = P->n_off.as<int>();
     int* wfoff = P->wf_off.as<int>();
-    hipLaunchKernelGGL(k_near, dim3(nblocks(B + 1, 4)), dim3(TB), 0, s, B, P->n, P->bx_leaf.as<int>(),
-                       P->bx_range.as<int2>(), uoff, P->u_idx.as<int>(), xoff, P->x_idx.as<int>(), woff,
-                       P->w_idx.as<int>(), noff, (int*)nullptr, wfoff, (int*)nullptr, 0);
-    exclusive_scan2<int>(P, noff, noff, nullptr, B + 1, wfoff, wfoff, B + 1, s);
-    P->n_idx.ensure((ucap + 2 * xcap) * 4);
-    P->wf_idx.ensure(xcap * 4);
-    hipLaunchKernelGGL(k_near, dim3(nblocks(B + 1, 4)), dim3(TB), 0, s, B, P->n, P->bx_leaf.as<int>(),
-                       P->bx_range.as<int2>(), uoff, P->u_idx.as<int>(), xoff, P->x_idx.as<int>(), woff,
-                       P->w_idx.as<int>(), noff, P->n_idx.as<int>(), wfoff, P->wf_idx.as<int>(), 1);
-    // leaf list and X-box list
-    P->tmp_f.ensure(size_t(B + 1) * 4 * 3);
-    int* fl = P->tmp_f.as<int>();
-    int* ol = fl + (B + 1);
-    int* ox = ol + (B + 1);
-    // the X-box flags are kept: a box's downward check potential is written by
-    // the P2L kernel exactly when its flag is set
-    P->xflag.ensure(size_t(B + 1) * 4);
-    int* fx = P->xflag.as<int>();
-    hipLaunchKernelGGL(k_flags, dim3(nblocks(B + 1)), dim3(TB), 0, s, B, P->bx_leaf.as<int>(), P->bx_range.as<int2>(),
-                       P->n, xoff, b2, fl, fx);
-    exclusive_scan2<int>(P, fl, ol, nullptr, B + 1, fx, ox, B + 1, s);
     // the leaf and X-box lists are sized by B, so that every size of the build
     // is read back once, below
     P->leaves.ensure(size_t(B) * 4);
     P->xboxes.ensure(size_t(B) * 4);
-    if (B > 0)
-        hipLaunchKernelGGL(k_compact2, dim3(nblocks(B), 2), dim3(TB), 0, s, B, fl, ol, P->leaves.as<int>(), fx, ox,
-                           P->xboxes.as<int>());
-    // work items per leaf (at most 64 targets each)
-    P->tmp_a.ensure(size_t(B + 1) * 8 + 64);
-    int* icnt = P->tmp_a.as<int>();
-    int* ioff = icnt + (B + 1);
-    hipLaunchKernelGGL(k_item_count, dim3(nblocks(B + 1)), dim3(TB), 0, s, B, ol + B, P->leaves.as<int>(),
-                       P->bx_range.as<int2>(), icnt);
-    exclusive_scan<int>(P, icnt, ioff, B + 1, s);
+    P->tmp_f.ensure(size_t(B + 1) * 4 * 3);
+    int* ol = P->tmp_f.as<int>();
+    int* ox = ol + (B + 1);
+    int* ioff = ox + (B + 1);
+    // the X-box flags are kept: a box's downward check potential is written by
+    // the P2L kernel exactly when its flag is set
+    P->xflag.ensure(size_t(B + 1) * 4);
+    int* fx = P->xflag.as<int>();
+    const BoxLists bl{b2, ol, fx, ox, ioff, P->leaves.as<int>(), P->xboxes.as<int>()};
+    hipLaunchKernelGGL(k_near, dim3(nblocks(B + 1, 4)), dim3(TB), 0, s, B, P->n, P->bx_leaf.as<int>(),
+                       P->bx_range.as<int2>(), uoff, P->u_idx.as<int>(), xoff, P->x_idx.as<int>(), woff,
+                       P->w_idx.as<int>(), noff, (int*)nullptr, wfoff, (int*)nullptr, bl, 0);
+    scan_set(P, ScanSet{{noff, wfoff, ol, fx, ioff}, {noff, wfoff, ol, ox, ioff}, nullptr}, 5, B + 1, s);
+    P->n_idx.ensure((ucap + 2 * xcap) * 4);
+    P->wf_idx.ensure(xcap * 4);
+    hipLaunchKernelGGL(k_near, dim3(nblocks(B + 1, 4)), dim3(TB), 0, s, B, P->n, P->bx_leaf.as<int>(),
+                       P->bx_range.as<int2>(), uoff, P->u_idx.as<int>(), xoff, P->x_idx.as<int>(), woff,
+                       P->w_idx.as<int>(), noff, P->n_idx.as<int>(), wfoff, P->wf_idx.as<int>(), bl, 1);
     // sizes: leaves, X boxes, items, the input flags, list lengths X, U, W, near
     int hs[8];
     read_ints(P, s, {ol + B, ox + B, ioff + B, bad, xoff + B, uoff + B, woff + B, noff + B}, hs);

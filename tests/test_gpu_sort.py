@@ -1,4 +1,5 @@
-"""The point sort of the tree build at the edges of its tiles and merge groups.
+"""The point sort of the tree build at the edges of its tiles and merge groups,
+and the boxes made of it.
 
 Sorted keys and the permutation are whole numbers and have to be those of a
 stable sort by key: one partial or whole tile (1024 points), the first merge
@@ -55,3 +56,43 @@ def test_sort(n, ties):
     x2[few] = positions(n, "none", n + 2)[few]
     plan.rebuild(torch.from_numpy(x2).cuda())
     check(plan, x2)
+
+
+def boxes(key, leaf, max_depth):
+    """(level, begin, end) of every box, level by level in key order."""
+    out, front = [(0, 0, len(key))], [(0, len(key))]
+    for level in range(1, max_depth + 1):
+        shift = np.uint64(3 * (21 - level))
+        nxt = []
+        for b, e in front:
+            cut = np.flatnonzero(np.diff(key[b:e] >> shift)) + 1 + b
+            ends = np.concatenate([[b], cut, [e]])
+            nxt += [(int(p), int(q)) for p, q in zip(ends[:-1], ends[1:])]
+        if not nxt:
+            break
+        out += [(level, p, q) for p, q in nxt]
+        front = [(p, q) for p, q in nxt if q - p > leaf and level < max_depth]
+    return out
+
+
+@pytest.mark.parametrize("n,leaf", [(300, 64), (5000, 16), (5000, 2), (40000, 2)])
+def test_boxes(n, leaf):
+    """Levels split by whole waves and, with more than 32 boxes to split, eight
+    boxes a wave; box scans in one block and (over 16384 boxes) in tiles.  The
+    box list is exact; the sums are over all pairs, so they also tell whether
+    the leaf, X-box and work-item lists made of those scans are whole."""
+    print(f"boxes n={n} leaf={leaf}", flush=True)
+    x = positions(n, "none", n)
+    dev = torch.from_numpy(x).cuda()
+    plan = Plan(dev, p=6, leaf_size=leaf, root=((0.0, 0.0, 0.0), 1.0))
+    t = plan.tree()
+    got = list(zip(np.asarray(t["level"]).tolist(), np.asarray(t["begin"]).tolist(), np.asarray(t["end"]).tolist()))
+    assert got == boxes(np.sort(morton(x)), leaf, 21)
+    q = torch.rand(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    u, _ = plan.evaluate(q)
+    sel = torch.arange(0, n, max(1, n // 200), device="cuda")
+    r = torch.cdist(dev[sel], dev, compute_mode="donot_use_mm_for_euclid_dist")
+    ref = (torch.where(r > 0, 1.0 / r, torch.zeros_like(r)) @ q.double()) / (4 * np.pi)
+    err = ((u[sel].double() - ref).norm() / ref.norm()).item()
+    print(f"  potential against all pairs: {err:.1e}", flush=True)
+    assert err < 1e-4   # p = 6 truncation is below 1e-5; one missing box of points is 1e-3 and more
