@@ -896,6 +896,26 @@ __device__ inline void moment_terms(const double* m, double k1, const double y[3
     for (int d = 0; d < 3; ++d) E[d] = 2.0 * k1 * (m[1 + d] - m[5 + d] - Q * y[d]);
 }
 
+// The leaf evaluation's blocks: the first `head` items (the heaviest) in
+// 1 << kFarParts parts of their targets, one block each, the others in 1 << parts.
+constexpr int kFarParts = 3;
+struct FarSplit {
+    int head, parts;
+    int blocks(int items) const { return (head << kFarParts) + ((items - head) << parts); }
+};
+struct FarPart {
+    int leaf, first, nt;   // leaf, first target and targets of a block (none: nt <= 0)
+};
+
+__device__ inline FarPart far_part(const int2* __restrict__ items, FarSplit s, const int2* __restrict__ range) {
+    const int blk = blockIdx.x, rest = blk - (s.head << kFarParts);
+    const int sh = rest < 0 ? kFarParts : s.parts, at = rest < 0 ? blk : rest;
+    const int2 it = items[(rest < 0 ? 0 : s.head) + (at >> sh)];
+    const int all = min(64, range[it.x].y - it.y), per = (all + (1 << sh) - 1) >> sh;
+    const int off = (at & ((1 << sh) - 1)) * per;
+    return FarPart{it.x, it.y + off, min(per, all - off)};
+}
+
 __device__ inline int far_lanes(int nt) { return nt <= 8 ? 8 : nt <= 16 ? 4 : nt <= 32 ? 2 : 1; }
 
 __device__ inline float far_sum(float v, int S) {
@@ -1060,7 +1080,7 @@ __device__ __forceinline__ void far_item(int b, int first, int nt, int b2, const
 }
 
 template <int NP, bool BWD>
-__global__ __launch_bounds__(256) void k_far(const int2* __restrict__ items, int b2,
+__global__ __launch_bounds__(256) void k_far(const int2* __restrict__ items, FarSplit split, int b2,
                                              const int4* __restrict__ anchor, const int2* __restrict__ range,
                                              const int* __restrict__ woff, const int* __restrict__ widx,
                                              const float4* __restrict__ pts, const float4* __restrict__ src2,
@@ -1071,11 +1091,11 @@ __global__ __launch_bounds__(256) void k_far(const int2* __restrict__ items, int
     __shared__ float red[4 * NV * 64];
     __shared__ float4 stage[NP];
     __shared__ float stage2[BWD ? NP : 1];
-    const int2 it = items[blockIdx.x];
-    const int b = it.x;
-    const int nt = min(64, range[b].y - it.y);
+    const FarPart it = far_part(items, split, range);
+    const int b = it.leaf, first = it.first, nt = it.nt;
+    if (nt <= 0) return;   // whole block
 #define KIFMM_FAR_ITEM(SV)                                                                                        \
-    far_item<NP, BWD, SV>(b, it.y, nt, b2, anchor, woff, widx, pts, src2, phi_d, phi_u, rhs_stride, surf, n, geo, \
+    far_item<NP, BWD, SV>(b, first, nt, b2, anchor, woff, widx, pts, src2, phi_d, phi_u, rhs_stride, surf, n, geo, \
                           cst, N, out, stage, stage2, red)
     switch (far_lanes(nt)) {
     case 8: KIFMM_FAR_ITEM(8); break;
@@ -1255,7 +1275,7 @@ __device__ __forceinline__ void far_grad_item(int b, int first, int nt, int b2, 
 }
 
 template <int NP>
-__global__ __launch_bounds__(256) void k_far_grad(const int2* __restrict__ items, int b2,
+__global__ __launch_bounds__(256) void k_far_grad(const int2* __restrict__ items, FarSplit split, int b2,
                                                   const int4* __restrict__ anchor, const int2* __restrict__ range,
                                                   const int* __restrict__ woff, const int* __restrict__ widx,
                                                   const float4* __restrict__ pts, const float* __restrict__ phi_d,
@@ -1264,11 +1284,11 @@ __global__ __launch_bounds__(256) void k_far_grad(const int2* __restrict__ items
                                                   const float* __restrict__ nearg, float* __restrict__ grad) {
     __shared__ float red[4 * 10 * 64];
     __shared__ float4 stage[NP];
-    const int2 it = items[blockIdx.x];
-    const int b = it.x;
-    const int nt = min(64, range[b].y - it.y);
+    const FarPart it = far_part(items, split, range);
+    const int b = it.leaf, first = it.first, nt = it.nt;
+    if (nt <= 0) return;   // whole block
 #define KIFMM_FARG_ITEM(SV)                                                                                      \
-    far_grad_item<NP, SV>(b, it.y, nt, b2, anchor, woff, widx, pts, phi_d, phi_u, surf, n, geo, cst, out, nearg, \
+    far_grad_item<NP, SV>(b, first, nt, b2, anchor, woff, widx, pts, phi_d, phi_u, surf, n, geo, cst, out, nearg, \
                           grad, stage, red)
     switch (far_lanes(nt)) {
     case 8: KIFMM_FARG_ITEM(8); break;
@@ -1703,6 +1723,23 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
     if (rec) record_phase(P, 4, s);
 }
 
+// A leaf with a long W list is a serial chain (1.6 us a source with 64
+// targets).  Below two rounds of the chip (256 CUs, 8 blocks each) the launch
+// lasts about as long as its longest items, so the heaviest go in parts: 254
+// to 91 us for 55k points in platelets (2,758 items), 45 to 34 for 100,003
+// clustered points (3,157).  Systems of few items are divided altogether, to
+// fill the chip (10,000 points, 376 items: 21 to 11 us).  Above, whole items
+// fill it and parts only stage each source more often (131,071 points, 5,787
+// items: 26 us whole, 35 in parts).
+constexpr int64_t kFarHead = 256, kFarFew = 2048, kFarMany = 4096;
+FarSplit far_split(const kifmm_plan* P) {
+    const int64_t n = P->n_items;
+    if (n >= kFarMany) return FarSplit{0, 0};
+    int parts = 0;
+    while (parts < kFarParts && (n << parts) < kFarFew) ++parts;
+    return FarSplit{int(std::min(n, kFarHead)), parts};
+}
+
 template <int NP>
 void far_impl(kifmm_plan* P, bool bwd, float* out_a, float* out_b, hipStream_t s, int rhs, bool acc, bool near,
               const StokesFrames* sf, bool sorted) {
@@ -1718,14 +1755,17 @@ void far_impl(kifmm_plan* P, bool bwd, float* out_a, float* out_b, hipStream_t s
         for (int d = 0; d < 3; ++d) fo.o[d] = P->lo[d] + 0.5 * P->side;
         fo.k1 = 2.0 * M_PI * P->c / (3.0 * P->side * P->side * P->side);
     }
+    const FarSplit split = far_split(P);
     size_t stride = size_t(P->B) * NP;
     if (bwd)
-        hipLaunchKernelGGL((k_far<NP, true>), dim3(unsigned(P->n_items)), dim3(256), 0, s, P->items_far.as<int2>(), b2,
+        hipLaunchKernelGGL((k_far<NP, true>), dim3(unsigned(split.blocks(int(P->n_items)))), dim3(256), 0, s,
+                           P->items_far.as<int2>(), split, b2,
                            P->bx_anchor.as<int4>(), P->bx_range.as<int2>(), P->wf_off.as<int>(), P->wf_idx.as<int>(),
                            P->pts.as<float4>(), P->src2.as<float4>(), P->phi_d.as<float>(), P->phi_u.as<float>(),
                            stride, op.surf.as<float4>(), op.n, geo, float(P->c), P->N, fo);
     else
-        hipLaunchKernelGGL((k_far<NP, false>), dim3(unsigned(P->n_items)), dim3(256), 0, s, P->items_far.as<int2>(), b2,
+        hipLaunchKernelGGL((k_far<NP, false>), dim3(unsigned(split.blocks(int(P->n_items)))), dim3(256), 0, s,
+                           P->items_far.as<int2>(), split, b2,
                            P->bx_anchor.as<int4>(), P->bx_range.as<int2>(), P->wf_off.as<int>(), P->wf_idx.as<int>(),
                            P->pts.as<float4>(), (const float4*)nullptr, P->phi_d.as<float>() + rhs * stride,
                            P->phi_u.as<float>() + rhs * stride, stride, op.surf.as<float4>(), op.n, geo, float(P->c),
@@ -1742,9 +1782,10 @@ void far_grad_impl(kifmm_plan* P, float* pot, float* field, float* grad, hipStre
         for (int d = 0; d < 3; ++d) fo.o[d] = P->lo[d] + 0.5 * P->side;
         fo.k1 = 2.0 * M_PI * P->c / (3.0 * P->side * P->side * P->side);
     }
+    const FarSplit split = far_split(P);
     const size_t stride = size_t(P->B) * NP;
-    hipLaunchKernelGGL((k_far_grad<NP>), dim3(unsigned(P->n_items)), dim3(256), 0, s, P->items_far.as<int2>(),
-                       int(P->bfar), P->bx_anchor.as<int4>(), P->bx_range.as<int2>(), P->wf_off.as<int>(),
+    hipLaunchKernelGGL((k_far_grad<NP>), dim3(unsigned(split.blocks(int(P->n_items)))), dim3(256), 0, s, P->items_far.as<int2>(),
+                       split, int(P->bfar), P->bx_anchor.as<int4>(), P->bx_range.as<int2>(), P->wf_off.as<int>(),
                        P->wf_idx.as<int>(), P->pts.as<float4>(), P->phi_d.as<float>() + rhs * stride,
                        P->phi_u.as<float>() + rhs * stride, op.surf.as<float4>(), op.n, geo, float(P->c), fo,
                        P->nearg.as<float>(), grad);
