@@ -304,7 +304,7 @@ __device__ inline void load8(float* b, const float* __restrict__ p) {
 // also lo.lo + hi.lo2 + lo2.hi.  Three pieces hold an FP32 number whole and
 // the six products leave out terms below 2^-24 of the largest, so PIECES = 3
 // is FP32 arithmetic at 16 / 6 of the FP32 matrix rate (1M clustered points,
-// rank 116: 2.6 to 1.2 ms a launch).
+// rank 116, beside the near field: 2.6 to 1.7 ms a launch).
 // A wave none of whose targets has the slot passes its products over.
 template <int NP, int PIECES, int CB, bool STK>
 __global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void k_m2l(TaskTable tt, int nblk, int ntile, int nsplit, int nrhs,

@@ -58,6 +58,24 @@ def test_sort(n, ties):
     check(plan, x2)
 
 
+@pytest.mark.parametrize("ties", ["none", "many"])
+def test_sort_by_passes(ties):
+    """Above 524288 points (and above as many displaced ones, here some 9 for
+    each that moves) the sort goes by digits of the key, equal keys by index."""
+    n = (1 << 19) + 1 if ties == "many" else 4_000_000
+    print(f"sort by passes n={n} ties={ties}", flush=True)
+    x = positions(n, ties, n)
+    plan = Plan(torch.from_numpy(x).cuda(), p=3, leaf_size=512, max_depth=8, root=((0.0, 0.0, 0.0), 1.0))
+    check(plan, x)
+    few = np.random.default_rng(n + 1).random(n) < 0.02
+    few[: n // 2] = False   # these move onto points of the first half
+    x[few] = x[:n // 2][np.random.default_rng(5).integers(0, n // 2, int(few.sum()))]
+    x[: n // 2][::50] = positions(n, "none", n + 2)[: n // 2][::50]
+    plan.rebuild(torch.from_numpy(x).cuda())
+    check(plan, x)
+    print("  ", plan.build_stats(), flush=True)
+
+
 def boxes(key, leaf, max_depth):
     """(level, begin, end) of every box, level by level in key order."""
     out, front = [(0, 0, len(key))], [(0, len(key))]
