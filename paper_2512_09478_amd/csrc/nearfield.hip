@@ -22,9 +22,10 @@
 // a wave copies 64 staged positions at a time out of the runs of contiguous
 // points that the tree build leaves, and the next batch is read while one is
 // summed.  Reading box by box between barriers left the waves waiting for 58 %
-// of their time (1M clustered points, alone: 0.84 ms forward and 1.36 ms
-// backward; now 0.60 and 1.07 ms, 42 and 23 TFLOP/s at 20 FLOP per pair:
-// 3 sub, 5 for r^2, rsqrt, 4 for q/r and q/r^3, 7 for the four sums).
+// of their time (1M clustered points, alone with the chip full: 0.84 ms forward
+// and 1.36 ms backward; now 0.60 and 1.07 ms, 42 and 23 TFLOP/s at 20 FLOP per
+// pair: 3 sub, 5 for r^2, rsqrt, 4 for q/r and q/r^3, 7 for the four sums; the
+// forward launch alone, at the four blocks per CU it takes, 0.80 ms).
 #include <float.h>
 #include <math.h>
 
