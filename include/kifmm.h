@@ -116,7 +116,7 @@ typedef struct {
 void kifmm_default_options(kifmm_options* opts);
 
 /*
- * Build a plan: root cube, Morton keys, radix sort, octree (Section 2.2,
+ * Build a plan: root cube, Morton keys, sort, octree (Section 2.2,
  * leaves with at most leaf_size = M points), interaction lists, and the
  * FP64 operator precompute (cached per kernel, p and pinv_rtol).
  *   positions  device, [N][3] double, caller order; rounded to FP32 for the
@@ -142,7 +142,7 @@ int kifmm_setup_ex(const double* positions, int64_t N, int kernel, int p, int le
  * order: the keys are formed in that order, the points out of order with a
  * neighbour are sorted on their own and merged back into the rest (when the
  * rest is in order and they are at most a quarter of the points; otherwise
- * the full radix sort runs).  The result is the same order as a fresh
+ * the full sort runs).  The result is the same order as a fresh
  * set-up's.  Synchronises `stream`.
  */
 int kifmm_rebuild(kifmm_handle h, const double* positions, void* stream);
@@ -372,7 +372,7 @@ int kifmm_get_counts(kifmm_handle h, int64_t out[10]);
  * rebuilds), out[1] builds that started from the previous build's order (a
  * rebuild with that order at hand), out[2] of those, the ones whose sort was
  * finished that way (the points out of order with a neighbour sorted on their
- * own and merged back into the rest); the others ran the full radix sort.
+ * own and merged back into the rest); the others ran the full sort.
  * Either way the order is the same: by key, ties by caller index.
  */
 int kifmm_get_build_stats(kifmm_handle h, int64_t out[3]);
