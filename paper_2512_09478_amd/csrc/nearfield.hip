@@ -193,10 +193,12 @@ struct Staged {
                 while (meet) {
                     const int k = __builtin_ctzll(meet);
                     meet &= meet - 1;
-                    const int dst = __builtin_amdgcn_readlane(e.y, k);
+                    // lane k need not be one of the lanes behind dst: all three reads with every lane on
+                    const int src = __builtin_amdgcn_readlane(e.x, k), dst = __builtin_amdgcn_readlane(e.y, k),
+                              img = __builtin_amdgcn_readlane(e.z, k);
                     const bool in = pos >= dst;
-                    from = in ? __builtin_amdgcn_readlane(e.x, k) - dst : from;
-                    code = in ? __builtin_amdgcn_readlane(e.z, k) : code;
+                    from = in ? src - dst : from;
+                    code = in ? img : code;
                 }
             }
             if (pos < hi) {
