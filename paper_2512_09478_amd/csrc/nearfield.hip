@@ -290,14 +290,14 @@ __device__ inline void near_units(const NearArgs& a, const float4* __restrict__ 
             st.read(run, nr, d, dn, 0, min(CAP, total), a.cell, pts, src2, ckey);
             for (int b0 = 0; b0 < total; b0 += CAP) {
                 const int m = min(CAP, total - b0);
-                const int tested = pass ? m : min(max(own - b0, 0), m);
+                const int untested = pass ? 0 : min(max(total - own - b0, 0), m);   // the leaf's own points come last
                 __syncthreads();
                 st.write(sh, m);
                 __syncthreads();
                 if (b0 + CAP < total)
                     st.read(run, nr, d, dn, b0 + CAP, min(CAP, total - b0 - CAP), a.cell, pts, src2, ckey);
-                for_sources<UNROLL>(nm, 0, tested, [&](int j) { pair(std::true_type{}, j, v); });
-                for_sources<UNROLL>(nm, tested, m, [&](int j) { pair(std::false_type{}, j, v); });
+                for_sources<UNROLL>(nm, 0, untested, [&](int j) { pair(std::false_type{}, j, v); });
+                for_sources<UNROLL>(nm, untested, m, [&](int j) { pair(std::true_type{}, j, v); });
             }
             // every sum of v[0] has 1/r as a factor, and any number times
             // infinity is not finite

@@ -1370,12 +1370,13 @@ __global__ void k_counts(int B, const int* __restrict__ leafflag, const int2* __
 
 // One wave per leaf: its near list as runs of contiguous sorted points, then
 // its items (up to 64 targets each) one per lane.
-// The runs: the leaf itself first (the only one that must hold pairs at
-// distance zero), then the other entries in list order, neighbouring entries
-// of one image whose point ranges touch joined (siblings do: about half the
-// entries go).  A run is (first point, staged position of the first point,
-// image code, 0); run[nruns] holds the number of staged points.  They start at
-// noff[b] + b, so that every leaf has room for its entries and that last one.
+// The runs: the entries in list order, neighbouring entries of one image whose
+// point ranges touch joined (siblings do: about half the entries go), and last
+// the leaf itself (the only one that must hold pairs at distance zero, and the
+// largest terms: added first they would round every term after them).  A run
+// is (first point, staged position of the first point, image code, 0);
+// run[nruns] holds the number of staged points.  They start at noff[b] + b, so
+// that every leaf has room for its entries and that last one.
 // A near item is (first target, targets, start of the leaf's runs, their
 // number), (points of the leaf, staged points, 0, 0): one read starts a block.
 __global__ __launch_bounds__(256) void k_item_fill(int nl, const int* __restrict__ leaves,
@@ -1392,13 +1393,12 @@ __global__ __launch_bounds__(256) void k_item_fill(int nl, const int* __restrict
     const int n0 = noff[b], n1 = noff[b + 1];
     int4* run = runs + n0 + b;
     const uint64_t lt = lane_lt_mask();
-    int nr = 1, staged = r.y - r.x;
-    if (lane == 0) run[0] = make_int4(r.x, 0, 0, 0);
+    int nr = 0, staged = 0;
     int last_end = -1, last_code = -1;   // end and image of the entry before this chunk
     for (int k0 = n0; k0 < n1; k0 += 64) {
         const int k = k0 + lane;
         const int e = k < n1 ? nidx[k] : b;
-        const bool use = k < n1 && e != b;   // the leaf itself is run 0
+        const bool use = k < n1 && e != b;   // the leaf itself is the last run
         const int2 ra = use ? range[img_box(e)] : make_int2(0, 0);
         const int code = use ? e >> kShiftBits : -1, end = use ? ra.y : -1;
         int pe = __shfl_up(end, 1, 64), pc = __shfl_up(code, 1, 64);
@@ -1419,6 +1419,9 @@ __global__ __launch_bounds__(256) void k_item_fill(int nl, const int* __restrict
         last_end = __shfl(end, 63, 64);
         last_code = __shfl(code, 63, 64);
     }
+    if (lane == 0) run[nr] = make_int4(r.x, staged, 0, 0);
+    ++nr;
+    staged += r.y - r.x;
     if (lane == 0) run[nr] = make_int4(0, staged, 0, 0);
     const unsigned long long src = staged;
     const unsigned long long nfar = (b >= b2 ? 1 : 0) + (woff[b + 1] - woff[b]);
