@@ -39,8 +39,11 @@ namespace kifmm {
 
 namespace {
 
-// source points staged per batch: kernels with one and with two arrays per source
-constexpr int NF_ONE = 512, NF_GRAD = 768, NF_TWO = 512;
+// source points staged per batch: kernels with one and with two arrays per
+// source, and with two arrays and clump keys (at 512 these need 91 registers,
+// and four blocks of them leave a CU no room for the M2L's: 200,000 pebbles,
+// forces and gradients, 857 us against 802)
+constexpr int NF_ONE = 512, NF_GRAD = 768, NF_TWO = 512, NF_KEYS = 256;
 
 // near-field blocks wanted before the items of a small system are no longer divided
 constexpr int kNearFill = 1024;
@@ -53,7 +56,11 @@ constexpr int kNearFill = 1024;
 // 2.63 with six, 2.65 uncapped; 262,147 with field gradient 0.77 against 0.77,
 // 0.97 and 1.01 ms).  With many points per leaf the near field is most of the
 // work (8.4M Plummer points, p = 8: 10 of 17 ms) and takes six.
+// The kernels are compiled for six blocks per CU (at most 80 registers), none
+// of them with scratch memory: bounds of seven and eight made six of the eight
+// forms spill.
 constexpr int kNearBlocks = 4, kNearBlocksDense = 6, kNearDense = 64;
+
 
 // The gathers precede the near field on the caller's stream and zero its counter.
 __global__ void k_gather(int64_t N, const float4* __restrict__ xs, const int* __restrict__ perm,
@@ -160,10 +167,15 @@ struct NearShared {
     int next[2];   // the block's next unit, in turns
 };
 
-// The source points a thread copies of one batch.
+typedef float nv4 __attribute__((ext_vector_type(4)));
+
+// The source points a thread copies of one batch.  (p2 as native vectors: an
+// array of float4 structures stayed in scratch memory, stored and read back
+// every batch.)
 template <int CAP, bool TWO, bool KEY>
 struct Staged {
-    float4 p[CAP / 256], p2[TWO ? CAP / 256 : 1];
+    float4 p[CAP / 256];
+    nv4 p2[TWO ? CAP / 256 : 1];
     int key[KEY ? CAP / 256 : 1];
 
     // Read the points at positions [b0, b0 + m) of the runs; a wave takes 64
@@ -204,7 +216,7 @@ struct Staged {
             if (pos < hi) {
                 const size_t at = size_t(from + pos);
                 p[c] = pts[at];
-                if (TWO) p2[c] = src2[at];
+                if (TWO) p2[c] = reinterpret_cast<const nv4*>(src2)[at];
                 if (KEY) key[c] = ckey[at];
                 if (code) {
                     int sx, sy, sz;
@@ -224,7 +236,7 @@ struct Staged {
             const int at = c * 256 + int(threadIdx.x);
             if (at < m) {
                 sh.p[at] = p[c];
-                if (TWO) sh.p2[at] = p2[c];
+                if (TWO) reinterpret_cast<nv4*>(sh.p2)[at] = p2[c];
                 if (KEY) sh.key[at] = key[c];
             }
         }
@@ -266,7 +278,6 @@ template <int CAP, bool TWO, bool KEY, int NV, int UNROLL, class Load, class Pai
 __device__ inline void near_units(const NearArgs& a, const float4* __restrict__ pts, const float4* __restrict__ src2,
                                   const int* __restrict__ ckey, NearShared<CAP, TWO, KEY, NV>& sh, Load load,
                                   Pair pair, Store store) {
-    static_assert(sizeof(float) * 4 * NV * 64 <= sizeof(float4) * CAP * (TWO ? 2 : 1), "reduction fits the staging");
     const int lane = threadIdx.x & 63;
     int unit = blockIdx.x;
     int4 i0 = a.items[2 * size_t(unit / a.parts)], i1 = a.items[2 * size_t(unit / a.parts) + 1];
@@ -316,7 +327,7 @@ __device__ inline void near_units(const NearArgs& a, const float4* __restrict__ 
 // EXCL: pairs whose clump keys (ckey, sorted) are equal are left out, which
 // drops the pairs of pebbles of one clump and the self pair.
 template <bool EXCL>
-__global__ __launch_bounds__(256, 8) void k_p2p(NearArgs a, const float4* __restrict__ pts, float cst,
+__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p(NearArgs a, const float4* __restrict__ pts, float cst,
                                              float4* __restrict__ nearv, const int* __restrict__ ckey) {
     __shared__ NearShared<NF_ONE, false, EXCL, 4> sh;
     float4 x;
@@ -344,7 +355,7 @@ __global__ __launch_bounds__(256, 8) void k_p2p(NearArgs a, const float4* __rest
 
 // Near field of monopoles q_j and dipoles m_j (src2 = (q, m) sorted):
 //   u += q_j/r - m_j.r/r^3,  E = -grad u += r (q_j/r^3 - 3 m_j.r/r^5) + m_j/r^3.
-__global__ __launch_bounds__(256) void k_p2p_dip(NearArgs a, const float4* __restrict__ pts,
+__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_dip(NearArgs a, const float4* __restrict__ pts,
                                                  const float4* __restrict__ src2, float cst,
                                                  float4* __restrict__ nearv) {
     __shared__ NearShared<NF_TWO, true, false, 4> sh;
@@ -375,7 +386,7 @@ __global__ __launch_bounds__(256) void k_p2p_dip(NearArgs a, const float4* __res
 // - 15 (m.r) r_a r_b / r^7.  (u, E) go to nearv, dE/dx (xx yy zz xy xz yz)
 // to nearg.
 template <bool DIP>
-__global__ __launch_bounds__(256) void k_p2p_grad(NearArgs a, const float4* __restrict__ pts,
+__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_grad(NearArgs a, const float4* __restrict__ pts,
                                                   const float4* __restrict__ src2, float cst,
                                                   float4* __restrict__ nearv, float* __restrict__ nearg) {
     constexpr int CAP = DIP ? NF_TWO : NF_GRAD;
@@ -441,12 +452,12 @@ __global__ __launch_bounds__(256) void k_p2p_grad(NearArgs a, const float4* __re
 //   qbar_k = psi_k,  xbar_k = -ubar_k E_k - H_k Ebar_k - q_k E_psi,k
 // where E, H come from the charges q and psi, E_psi from monopoles ubar and
 // dipoles Ebar (psi = sum ubar K - Ebar . G).
-// Compiled for six blocks per CU (at most 85 registers).
 template <bool EXCL>
-__global__ __launch_bounds__(256, 7) void k_p2p_bwd(NearArgs na, const float4* __restrict__ pts,
+__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_bwd(NearArgs na, const float4* __restrict__ pts,
                                                     const float4* __restrict__ src2, float cst,
                                                     float4* __restrict__ nearv, const int* __restrict__ ckey) {
-    __shared__ NearShared<NF_TWO, true, EXCL, 9> sh;
+    constexpr int CAP = EXCL ? NF_KEYS : NF_TWO;
+    __shared__ NearShared<CAP, true, EXCL, 9> sh;
     // The adjoint combination xbar_k = -ubar_k E_k - H_k Ebar_k - q_k E_psi,k
     // is summed pair by pair (r = x_k - y_j, c applied at the end):
     //   xbar += r [-(ubar_k q_j + q_k ubar_j)/r^3 - 3 (q_j r.Ebar_k - q_k r.Ebar_j)/r^5]
@@ -456,7 +467,7 @@ __global__ __launch_bounds__(256, 7) void k_p2p_bwd(NearArgs na, const float4* _
     // psi is kept as its two sums (v[7] ubar_j / r, v[8] r.Ebar_j / r^3)
     float4 x, a;
     int ck = 0;
-    near_units<NF_TWO, true, EXCL, 9, 1>(
+    near_units<CAP, true, EXCL, 9, 1>(
         na, pts, src2, ckey, sh,
         [&](int i, bool act) {
             x = act ? pts[i] : make_float4(0, 0, 0, 0);
@@ -523,7 +534,7 @@ __global__ void k_gather_stokes(int64_t N, const float4* __restrict__ xs, const 
 // from stk (sorted); written as cst * u to out (sorted), with the unscaled sum
 // of (r.f)/r^3 (the near part of the pressure, times 4 pi) in the fourth
 // component.
-__global__ __launch_bounds__(256) void k_p2p_stokes(NearArgs a, const float4* __restrict__ xs,
+__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_stokes(NearArgs a, const float4* __restrict__ xs,
                                                     const float4* __restrict__ stk, float cst,
                                                     float4* __restrict__ out) {
     __shared__ NearShared<NF_TWO, true, false, 4> sh;
