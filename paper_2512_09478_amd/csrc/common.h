@@ -293,7 +293,9 @@ struct kifmm_plan {
     int64_t builds = 0, resort_steps = 0, resort_hits = 0;   // builds; those that tried / completed the re-sort
     kifmm::PhaseEvents events;
     kifmm::SideStream nearq;   // near-field stream
-    kifmm::DBuf near_taken;    // int: the near field's work counter, zeroed by the gather before it
+    // per-call words, zeroed by the gathers: [0] the near field's work counter,
+    // [1 + r] the bits of the largest P2M check potential of right-hand side r (see note_max)
+    kifmm::DBuf words;
     bool fwd_valid = false;   // densities of right-hand side 0 and pts hold the last forward pass
     bool fwd_excl = false;    // ... and that pass left out the pairs of pebbles of one clump
     // input errors found on the device (clump offsets): int word, cleared by kifmm_synchronize

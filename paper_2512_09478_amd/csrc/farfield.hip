@@ -166,12 +166,23 @@ __device__ inline float add_slices(float acc, int i, int slice, float* red) {
     return slice == 0 ? acc + red[i] : 0.f;
 }
 
+// The bits of the largest |v| of a launch into *word (zero before), or those of
+// 1 where it is 2^-30 or more: then every wave with such a value stores the
+// same word, and the others, which take the maximum, cannot lower it.
+constexpr unsigned kTinyBits = 97u << 23;   // 2^-30
+__device__ inline void note_max(float v, unsigned* word) {
+    const unsigned m = __float_as_uint(fabsf(v));
+    if (__ballot(m >= kTinyBits)) *word = 0x3f800000u;
+    else if (m) atomicMax(word, m);
+}
+
+// (pmax: null, or the word of this right-hand side for the M2L's scaling)
 template <int NP>
 __global__ __launch_bounds__(2 * NP) void k_p2m(const int* __restrict__ leaves, int nleaves, int b2,
                                                 const int4* __restrict__ anchor, const int2* __restrict__ range,
                                                 const float4* __restrict__ pts, const float4* __restrict__ src2,
                                                 const float4* __restrict__ frc, const float4* __restrict__ surf,
-                                                int n, BoxGeom geo, float* __restrict__ psi_u) {
+                                                int n, BoxGeom geo, float* __restrict__ psi_u, unsigned* pmax) {
     __shared__ float4 sh[256];
     __shared__ float4 sh2[256];
     __shared__ float red[NP];
@@ -187,7 +198,9 @@ __global__ __launch_bounds__(2 * NP) void k_p2m(const int* __restrict__ leaves, 
     float acc = 0.f;
     points_to_surface<NP>(acc, pts, src2, frc, r.x, r.y, c, invw, s, act, slice, sh, sh2);
     acc = add_slices<NP>(acc, i, slice, red);
-    if (slice == 0) psi_u[size_t(b) * NP + i] = act ? acc : 0.f;
+    if (!act) acc = 0.f;
+    if (slice == 0) psi_u[size_t(b) * NP + i] = acc;
+    if (pmax) note_max(acc, pmax);
 }
 
 template <int NP>
@@ -304,7 +317,12 @@ __device__ inline void load8(float* b, const float* __restrict__ p) {
 // also lo.lo + hi.lo2 + lo2.hi.  Three pieces hold an FP32 number whole and
 // the six products leave out terms below 2^-24 of the largest, so PIECES = 3
 // is FP32 arithmetic at 16 / 6 of the FP32 matrix rate (1M clustered points,
-// rank 116, beside the near field: 2.6 to 1.7 ms a launch).
+// rank 116, beside the near field: 2.6 to 1.7 ms a launch).  The pieces have
+// FP32's exponents, so a value below 2^-110 would lose the last: where the
+// largest P2M check potential (pmax, by right-hand side) is below 2^-30 the
+// sources are multiplied by the power of two that brings it to 1, and the sums
+// divided by it.  Densities that still lose a piece are 2^-80 of that
+// potential, and no sum of densities reaches 2^60 of it.
 // A wave none of whose targets has the slot passes its products over.
 template <int NP, int PIECES, int CB, bool STK>
 __global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void k_m2l(TaskTable tt, int nblk, int ntile, int nsplit, int nrhs,
@@ -316,7 +334,7 @@ __global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void
                                              const uint4* __restrict__ ops3, const int4* __restrict__ anchor,
                                              BoxGeom geo,
                                              const float* __restrict__ s0, const float* __restrict__ s1,
-                                             const float* __restrict__ s2) {
+                                             const float* __restrict__ s2, const unsigned* __restrict__ pmax) {
     // the third pieces of a chunk (ops3) follow the others (ops) in LDS
     constexpr int RB = NP / 16, KC = NP / 32, WORDS = RB * 128, WORDS3 = PIECES == 3 ? RB * 64 : 0;
     __shared__ uint4 lds0[WORDS + WORDS3];
@@ -369,17 +387,25 @@ __global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void
     }
     __syncthreads();
     int j = next_slot(vmask, -1);   // block-uniform; kVPerOct when this slot range is empty
-    // split 0 of a target that the P2L kernel wrote starts from its X-list
-    // check potential (no other box's value is written before), the others
-    // from zero
-    v4f acc[CB][RB];
+    // exponents of the sources' factor (PIECES = 3), 127 where they stay as they are
+    int up[CB];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-        load_acc<NP>(acc[cb],
-                     (split == 0 && tgt[cb] >= 0 && psi_d && xflag[tgt[cb]])
-                         ? psi_d + size_t(cb % nrhs) * rhs_stride + size_t(tgt[cb]) * NP
-                         : nullptr,
-                     lane);
+    for (int cb = 0; cb < CB; ++cb) {
+        const int e = PIECES == 3 ? int(pmax[cb % nrhs] >> 23) : 127;
+        up[cb] = e < int(kTinyBits >> 23) ? min(254 - e, 253) : 127;
+    }
+    // split 0 of a target that the P2L kernel wrote starts from its X-list
+    // check potential (no other box's value is written before; it is added
+    // last where the sources are multiplied), the others from zero
+    v4f acc[CB][RB];
+    const float* start[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+        start[cb] = (split == 0 && tgt[cb] >= 0 && psi_d && xflag[tgt[cb]])
+                        ? psi_d + size_t(cb % nrhs) * rhs_stride + size_t(tgt[cb]) * NP
+                        : nullptr;
+        load_acc<NP>(acc[cb], up[cb] == 127 ? start[cb] : nullptr, lane);
+    }
     if (j < kVPerOct) {
         const int g8 = 8 * (lane >> 4);
         int kc = 0;
@@ -460,6 +486,7 @@ __global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         float rest = cur[cb][i];
+                        if constexpr (PIECES == 3) rest *= __uint_as_float(unsigned(up[cb]) << 23);
 #pragma unroll
                         for (int q = 0; q < PIECES; ++q) {
                             const __bf16 h = (__bf16)rest;
@@ -524,6 +551,15 @@ __global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void
         }
     }
     float* out = psi_m + size_t(split) * split_stride;
+    if constexpr (PIECES == 3)
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+            if (up[cb] != 127) {
+                v4f x[RB];
+                load_acc<NP>(x, start[cb], lane);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = acc[cb][rb] * __uint_as_float(unsigned(254 - up[cb]) << 23) + x[rb];
+            }
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
         store_acc<NP>(acc[cb], tgt[cb] >= 0 ? out + size_t(cb % nrhs) * rhs_stride + size_t(tgt[cb]) * NP : nullptr,
@@ -1455,7 +1491,7 @@ void launch_m2l_tile(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, const floa
                        nsplit, nrhs, P->nonleaf.as<int>(), P->bx_child.as<int2>(), P->vdense.as<int>(), b2,     \
                        vops_device(), phi_u, psi_d, P->xflag.as<int>(), psi_m, stride, sstride,                 \
                        ops[PCS == 1 ? 0 : 1]->as<uint4>(), ops[2]->as<uint4>(), P->bx_anchor.as<int4>(), geo,   \
-                       s3[0], s3[1], s3[2])
+                       s3[0], s3[1], s3[2], P->words.as<unsigned>() + 1 + rhs)
     if (stk3) {
         if (nrhs != 2) throw Error(KIFMM_ERR_STATE, "the framed Stokes M2L takes the sweep's two right-hand sides");
         if (pieces == 2) KIFMM_M2L_LAUNCH(2, true);
@@ -1475,8 +1511,7 @@ void launch_m2l_tile(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, const floa
 
 // sf: right-hand side `rhs` is the Stokeslet's fourth charge in per-box frames
 template <int NP>
-void launch_m2l(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, bool exact32, const StokesFrames* sf = nullptr) {
-    const int pieces = P->opt.precision == KIFMM_SPLIT_BF16 ? 2 : exact32 ? 1 : 3;
+void launch_m2l(kifmm_plan* P, int nrhs, int rhs, hipStream_t s, int pieces, const StokesFrames* sf = nullptr) {
     if (!P->cm) {
         const Operators& op = *P->ops;
         const DBuf* const ops[3] = {&op.m2l_f32, &op.m2l_bf16, &op.m2l_bf16_3};
@@ -1605,6 +1640,7 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
     // forces on clumps and Stokes flow) the rounding of either is 1e-5 to 1e-4
     // of it, and the FP32 instructions stay.
     const bool exact32 = fp32_m2l || P->kernel != KIFMM_LAPLACE || P->p >= 7;
+    const int pieces = P->opt.precision == KIFMM_SPLIT_BF16 ? 2 : exact32 ? 1 : 3;
     // right-hand side 1 of a Stokes sweep carries the fourth charge in per-box frames
     auto stk = [&](int r) { return sf != nullptr && r == 1; };
     const int B = int(P->B);
@@ -1637,7 +1673,8 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
         hipLaunchKernelGGL(k_p2m<NP>, dim3(unsigned(P->nleaves)), dim3(tpb), 0, s, P->leaves.as<int>(),
                            int(P->nleaves), b2, P->bx_anchor.as<int4>(), P->bx_range.as<int2>(), pts,
                            (r && !stk(r)) ? P->src2.as<float4>() : nullptr, stk(r) ? sf->frc : nullptr, surf, op.n,
-                           geo, P->psi_u.as<float>() + r * stride);
+                           geo, P->psi_u.as<float>() + r * stride,
+                           pieces == 3 ? P->words.as<unsigned>() + 1 + r : nullptr);
     if (rec) record_phase(P, 0, s);
     // downward check potentials of the boxes the P2L kernel sums (flagged in
     // xflag; the M2L and the compressed expansion read no other box's value
@@ -1694,9 +1731,9 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
     // V list (a Stokes sweep's second right-hand side in per-box frames)
     if (sf && (r0 != 0 || r1 != 2)) throw Error(KIFMM_ERR_STATE, "a Stokes sweep has right-hand sides 0 and 1");
     if (r1 - r0 == 2) {
-        launch_m2l<NP>(P, 2, 0, s, exact32, sf);
+        launch_m2l<NP>(P, 2, 0, s, pieces, sf);
     } else {
-        for (int r = r0; r < r1; ++r) launch_m2l<NP>(P, 1, r, s, exact32);
+        for (int r = r0; r < r1; ++r) launch_m2l<NP>(P, 1, r, s, pieces);
     }
     if (rec) record_phase(P, 3, s);
     if (aside && P->cm) KIFMM_HIP(hipStreamWaitEvent(s, P->nearq.mid, 0));

@@ -62,11 +62,13 @@ constexpr int kNearFill = 1024;
 constexpr int kNearBlocks = 4, kNearBlocksDense = 6, kNearDense = 64;
 
 
-// The gathers precede the near field on the caller's stream and zero its counter.
+// The gathers precede everything else of a call on the caller's stream and
+// zero its words: the near field's counter and the maximum of the right-hand
+// side they set.
 __global__ void k_gather(int64_t N, const float4* __restrict__ xs, const int* __restrict__ perm,
-                         const float* __restrict__ q, float4* __restrict__ pts, int* __restrict__ taken) {
+                         const float* __restrict__ q, float4* __restrict__ pts, int* __restrict__ words) {
     int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
-    if (i == 0) *taken = 0;
+    if (i == 0) words[0] = words[1] = 0;
     if (i >= N) return;
     float4 x = xs[i];
     x.w = q ? q[perm[i]] : 0.f;
@@ -74,9 +76,9 @@ __global__ void k_gather(int64_t N, const float4* __restrict__ xs, const int* __
 }
 
 __global__ void k_gather_adj(int64_t N, const int* __restrict__ perm, const float* __restrict__ gu,
-                             const float* __restrict__ ge, float4* __restrict__ src2, int* __restrict__ taken) {
+                             const float* __restrict__ ge, float4* __restrict__ src2, int* __restrict__ words) {
     int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
-    if (i == 0) *taken = 0;
+    if (i == 0) words[0] = words[2] = 0;
     if (i >= N) return;
     int j = perm[i];
     src2[i] = make_float4(gu ? gu[j] : 0.f, ge ? ge[3 * size_t(j)] : 0.f, ge ? ge[3 * size_t(j) + 1] : 0.f,
@@ -512,9 +514,9 @@ __global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_bwd(NearArgs na, 
 // from stk where a box's sources are summed.
 __global__ void k_gather_stokes(int64_t N, const float4* __restrict__ xs, const int* __restrict__ perm,
                                 const float* __restrict__ f, int pass, float4* __restrict__ pts,
-                                float4* __restrict__ src2, float4* __restrict__ stk, int* __restrict__ taken) {
+                                float4* __restrict__ src2, float4* __restrict__ stk, int* __restrict__ words) {
     int64_t i = blockIdx.x * int64_t(256) + threadIdx.x;
-    if (pass == 0 && i == 0) *taken = 0;   // the near field of pass 0 may still run in pass 1
+    if (pass == 0 && i == 0) words[0] = 0;   // the near field of pass 0 may still run in pass 1
     if (i >= N) return;
     const size_t j = size_t(perm[i]);
     const float fx = f[3 * j], fy = f[3 * j + 1], fz = f[3 * j + 2];
@@ -581,7 +583,7 @@ NearLaunch near_launch(kifmm_plan* P, bool images = true) {
     while (parts < 8 && P->n_items * parts < kNearFill) parts *= 2;
     const int units = int(P->n_items) * parts;
     const int per_cu = P->N > int64_t(kNearDense) * P->nleaves ? kNearBlocksDense : kNearBlocks;
-    return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->n_runs.as<int4>(), P->near_taken.as<int>(),
+    return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->n_runs.as<int4>(), P->words.as<int>(),
                                images ? float(P->side) : 0.f},
                       dim3(unsigned(std::min(units, device_cus() * per_cu)))};
 }
@@ -591,16 +593,16 @@ NearLaunch near_launch(kifmm_plan* P, bool images = true) {
 void launch_gather(kifmm_plan* P, const float* charges, const float* gpot, const float* gfield, bool adjoint,
                    hipStream_t s, bool points) {
     const int64_t N = P->N;
-    int* taken = static_cast<int*>(P->near_taken.ensure(sizeof(int)));
+    int* words = static_cast<int*>(P->words.ensure(3 * sizeof(int)));
     if (charges || points) {
         P->pts.ensure(size_t(N) * 16);
         hipLaunchKernelGGL(k_gather, dim3(unsigned((N + 255) / 256)), dim3(256), 0, s, N, P->xs.as<float4>(),
-                           P->perm.as<int>(), charges, P->pts.as<float4>(), taken);
+                           P->perm.as<int>(), charges, P->pts.as<float4>(), words);
     }
     if (adjoint) {
         P->src2.ensure(size_t(N) * 16);
         hipLaunchKernelGGL(k_gather_adj, dim3(unsigned((N + 255) / 256)), dim3(256), 0, s, N, P->perm.as<int>(), gpot,
-                           gfield, P->src2.as<float4>(), taken);
+                           gfield, P->src2.as<float4>(), words);
     }
 }
 
@@ -611,7 +613,7 @@ void launch_gather_stokes(kifmm_plan* P, const float* forces, int pass, hipStrea
     P->stk.ensure(size_t(N) * 16);
     hipLaunchKernelGGL(k_gather_stokes, dim3(unsigned((N + 255) / 256)), dim3(256), 0, s, N, P->xs.as<float4>(),
                        P->perm.as<int>(), forces, pass, P->pts.as<float4>(), P->src2.as<float4>(),
-                       P->stk.as<float4>(), static_cast<int*>(P->near_taken.ensure(sizeof(int))));
+                       P->stk.as<float4>(), static_cast<int*>(P->words.ensure(3 * sizeof(int))));
 }
 
 void launch_p2p_forward(kifmm_plan* P, hipStream_t s, bool excl) {
