@@ -56,7 +56,15 @@ enum kifmm_kernel {
 };
 
 enum kifmm_precision {
-    KIFMM_FP32 = 0,        /* every far-field product in FP32 (MFMA f32) */
+    KIFMM_FP32 = 0,        /* every far-field product in FP32 (MFMA f32), except
+                              the M2L of Laplace plans with p <= 6 (clump forces
+                              and Stokes sums aside): there both operands are
+                              split into three bf16 pieces, which hold the 24
+                              bits of an FP32 number, and multiplied by six bf16
+                              MFMA products with FP32 accumulation (what they
+                              leave out is below 2^-24 of the largest product).
+                              As near to 64-bit values as MFMA f32, for charges
+                              of one sign or both and down to 1e-35 */
     KIFMM_SPLIT_BF16 = 1   /* M2L products as bf16 hi/lo splits (three bf16 MFMA
                               products, FP32 accumulation); all else FP32 */
 };

@@ -1634,11 +1634,16 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
                 const StokesFrames* sf, bool fp32_m2l) {
     const Operators& op = *P->ops;
     // The FP32 path's M2L: six bf16 products round as little as the FP32
-    // instructions (against 64 bits the fields are as near or nearer), but
-    // differently.  Where the result is a small difference of large check
-    // potentials (one-signed masses, p >= 7; by the caller's word, fp32_m2l,
-    // forces on clumps and Stokes flow) the rounding of either is 1e-5 to 1e-4
-    // of it, and the FP32 instructions stay.
+    // instructions, but differently.  The rule is by kernel, p and call, not by
+    // the signs of the charges.  Laplace, p <= 6, against the FP64 oracle at
+    // 20,000 to 120,000 points (FP32 instructions, then six products): charges
+    // of both signs u 4.8e-7 and 5.3e-7, E 6.8e-7 and 5.8e-7 (uniform, p = 6), u
+    // 6.9e-7 and 6.2e-7, E 3.2e-7 and 0.9e-7 (clustered); of one sign u 2.5e-7
+    // and 2.5e-7, E 1.03e-5 and 0.99e-5 (uniform), E 1.74e-5 and 1.71e-5 (a
+    // concentrated sphere).  FP32 instructions stay where the rounding of
+    // either is 1e-5 to 1e-4 of the result and only its draw would change (p >=
+    // 7; by the caller's word, fp32_m2l, forces on clumps and Stokes flow), and
+    // for gravity.
     const bool exact32 = fp32_m2l || P->kernel != KIFMM_LAPLACE || P->p >= 7;
     const int pieces = P->opt.precision == KIFMM_SPLIT_BF16 ? 2 : exact32 ? 1 : 3;
     // right-hand side 1 of a Stokes sweep carries the fourth charge in per-box frames
