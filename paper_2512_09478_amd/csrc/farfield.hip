@@ -1772,7 +1772,11 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
 // clustered points (3,157).  Systems of few items are divided altogether, to
 // fill the chip (10,000 points, 376 items: 21 to 11 us).  Above, whole items
 // fill it and parts only stage each source more often (131,071 points, 5,787
-// items: 26 us whole, 35 in parts).
+// items: 26 us whole, 35 in parts).  Up to 1,024 items the list is in leaf
+// order, level by level: its head then holds the coarsest leaves, which have the
+// longest W lists, but not always the heaviest items.  Eight parts for all of
+// them there is no better: 617 items 122 us an evaluation, 124 all in eight; 822
+// items with the heaviest past the head 265 and 266.
 constexpr int64_t kFarHead = 256, kFarFew = 2048, kFarMany = 4096;
 FarSplit far_split(const kifmm_plan* P) {
     const int64_t n = P->n_items;
