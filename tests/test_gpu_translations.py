@@ -12,7 +12,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-# n points, leaf: about 4, 20 and 300 to 1,300 non-leaf boxes in the widest level
+# n points, leaf: up to 740 non-leaf boxes in the widest level (p = 2, 9000 points)
 @pytest.mark.parametrize("p,n,leaf", [(2, 300, 8), (2, 9000, 2), (3, 3000, 6), (4, 9000, 2), (5, 3000, 6), (6, 300, 4),
                                       (6, 9000, 3), (7, 2000, 6), (8, 2500, 6)])
 @pytest.mark.parametrize("m2l_rtol", [0.0, 1e-6])
