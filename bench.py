@@ -185,7 +185,18 @@ def stored_traffic(kernel, precision, workload, n):
     return None
 
 
-def roofline(res, n, precision, workload, npts):
+def m2l_arithmetic(precision, n, kernel):
+    """(peak, matrix products per useful one) of the M2L: three bf16 products on
+    the split path, six on the FP32 path of Laplace plans with p <= 6 (at most
+    152 surface points), else FP32 matrix instructions."""
+    if precision == "split_bf16":
+        return PEAK["bf16"], 3
+    if kernel == "laplace" and n <= 152:
+        return PEAK["bf16"], 6
+    return PEAK["fp32"], 1
+
+
+def roofline(res, n, precision, workload, npts, kernel="laplace"):
     """Roofline of the kernel with the most time per step: the M2L (one launch
     in the forward pass and one in the adjoint) or the forward P2P.  The
     per-launch time is the mean of that kernel's launches in a step, each
@@ -200,11 +211,12 @@ def roofline(res, n, precision, workload, npts):
         k = c.get("m2l_rank", n)
         flops = 2.0 * k * k * c["v_pairs"]
         per = 0.5 * m2l_total
-        peak = PEAK["bf16"] if precision == "split_bf16" else PEAK["fp32"]
+        peak, products = m2l_arithmetic(precision, n, kernel)
         ach = flops / (per * 1e-3) / 1e12
         return dict(kernel="k_m2l", bound="mfma", achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak,
                     traffic=stored_traffic("k_m2l", precision, workload, npts), per_launch_ms=per,
-                    work=f"2 k^2 x {c['v_pairs']} V pairs, k = {k} (surface size {n})")
+                    work=f"2 k^2 x {c['v_pairs']} V pairs, k = {k} (surface size {n}); "
+                         f"{products} matrix product{'s' if products > 1 else ''} each, counted once")
     return near_roofline(res, precision, workload, npts)
 
 
@@ -305,7 +317,7 @@ def run_largest(Plan, steps, warmup, m2l_rtol):
             "warmup": warmup, "ms_per_step": r["ms_per_step"], "particles_per_s": w.n / (r["ms_per_step"] * 1e-3),
             "t_tree_ms": r["t_tree_ms"], "t_fwd_ms": r["t_fwd_ms"], "t_adj_ms": r["t_adj_ms"],
             "phases_fwd_ms": r["phases_fwd_ms"], "phases_adj_ms": r["phases_adj_ms"], "counts": r["counts"],
-            "roofline": roofline(r, r["counts"]["surface_points"], "split_bf16", w.name, w.n)}
+            "roofline": roofline(r, r["counts"]["surface_points"], "split_bf16", w.name, w.n, w.kernel)}
 
 
 def run_f4(Plan, steps, warmup, m2l_rtol, paths=("split_bf16", "fp32"), check=True, nsample=256):
@@ -685,7 +697,7 @@ def main():
                                + (f"; particles move by N(0, {args.move}^2) per axis each step" if args.move else ""),
                    "name": w.name, "n": n, "p": w.p, "leaf_size": w.leaf_size, "path": head,
                    "m2l_rtol": args.m2l_rtol},
-        "roofline": roofline(H, ops_n, head, wkey, n),
+        "roofline": roofline(H, ops_n, head, wkey, n, w.kernel),
         # the forward near field beside it (the other kernel of the step)
         "roofline_near": near_roofline(H, head, wkey, n),
         "paths": {k: {"particles_per_s": n / (v["ms_per_step"] * 1e-3), "ms_per_step": v["ms_per_step"],
@@ -695,7 +707,7 @@ def main():
                       "t_tree_ms": v["t_tree_ms"], "t_fwd_ms": v["t_fwd_ms"], "t_adj_ms": v["t_adj_ms"],
                       "phases_fwd_ms": v["phases_fwd_ms"], "phases_adj_ms": v["phases_adj_ms"],
                       "tree_builds": v["builds"],
-                      "roofline": roofline(v, ops_n, k, wkey, n),
+                      "roofline": roofline(v, ops_n, k, wkey, n, w.kernel),
                       "roofline_near": near_roofline(v, k, wkey, n)}
                   for k, v in paths.items()},
         "counts": H["counts"],
