@@ -38,10 +38,15 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int WAVES = 4;
 
-// Boxes up to which the check-to-equivalent map takes one or two column blocks
-// of 16 boxes per block, and non-leaves of a level up to which M2M spreads its
-// row blocks as widely as they go
-constexpr int kC2eOne = 4096, kC2eTwo = 32768;
+// Boxes up to which the check-to-equivalent map takes one column block of 16
+// boxes per block, above it two; and non-leaves of a level up to which M2M
+// spreads its row blocks as widely as they go.  us an evaluation spends in the
+// upward and downward passes (p = 6), one and two column blocks: widest levels
+// of 4,096 boxes 98 + 61 and 115 + 100, of 32,000 boxes 321 + 242 and 302 + 236.
+// Four column blocks find no room beside the near field: 107,000 leaves 2,220
+// up, 505 with two (the evaluation 5.23 and 4.44 ms).  M2M spread and not, up:
+// 512 non-leaves in the widest level 98 and 154, 4,012 305 and 302.
+constexpr int kC2eOne = 4096;
 constexpr int kM2mFew = 1024;
 
 struct BoxGeom {
@@ -581,7 +586,7 @@ __global__ __launch_bounds__(256, STK || (PIECES == 3 && NP > 128) ? 2 : 3) void
 // accumulator layout, the operators (0.1-0.4 MB each) come from L2.  With few
 // boxes the launch is one chain of dependent reads and MFMA steps, so it takes
 // as many waves as there are row blocks (CB = NR = 1); with many it is bound by
-// operator reads and FP32 MFMA issue, and CB column blocks share each operator
+// operator reads and FP32 MFMA issue, and two column blocks share each operator
 // fragment.  Registers stay few in the first form: a block of ten waves starts
 // only on a CU with room for all of them beside the near field's (holding the
 // factors in registers ahead of the data needed 100 a wave, took as long alone
@@ -1584,15 +1589,8 @@ void launch_c2e(kifmm_plan* P, const int* list, int64_t b0, int64_t nb, const fl
                            xpsi, P->xflag.as<int>(), KP ? P->cm->q.as<uint4>() : nullptr, l2l, w1c, vc, phi,        \
                            P->bx_anchor.as<int4>(), geo, s3[0], s3[1], s3[2]);                                      \
     } while (0)
-    // four column blocks do not fit the registers of the wide or framed forms
-    if (boxes <= kC2eOne) {
-        KIFMM_C2E(true, 1);
-    } else if constexpr (NP == 320 || STK) {
-        KIFMM_C2E(false, 2);
-    } else {
-        if (boxes <= kC2eTwo) KIFMM_C2E(false, 2);
-        else KIFMM_C2E(false, 4);
-    }
+    if (boxes <= kC2eOne) KIFMM_C2E(true, 1);
+    else KIFMM_C2E(false, 2);
 #undef KIFMM_C2E
 }
 

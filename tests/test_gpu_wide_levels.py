@@ -1,7 +1,7 @@
 """Upward and downward passes on wide levels: the forms of the translation
-kernels that take two row blocks (above 1,024 non-leaves a level) and two or four
-column blocks (above 4,096 and 32,768 boxes), at every surface size, with the
-exact and the compressed M2L.
+kernels that take two row blocks (above 1,024 non-leaves a level) and two column
+blocks (above 4,096 boxes), at every surface size, with the exact and the
+compressed M2L.
 
 A small system, whose levels take the narrow forms, is compared with itself
 inside a large one whose other points carry nothing: the same boxes and
