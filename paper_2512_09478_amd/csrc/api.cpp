@@ -103,7 +103,8 @@ enum NearKind { NEAR_FORWARD, NEAR_BACKWARD, NEAR_DIPOLES, NEAR_GRAD, NEAR_GRAD_
 // The near field does not depend on the far-field sweep: it runs on the side
 // stream, forked from `s` after P2M (so that the sweep's first kernel is not
 // queued behind it) and joined back before the leaf evaluation, which adds it
-// to the far field.  Neither does P2L (`first`), which goes ahead of it there:
+// to the far field.  Neither does P2L (`first`, empty without X lists), which
+// goes ahead of it there:
 // on the caller's stream it added 50 to 90 us between the upward pass and the
 // M2L.
 void fork_near(kifmm_plan* P, NearKind kind, hipStream_t s, const std::function<void(hipStream_t)>& first,
@@ -114,8 +115,10 @@ void fork_near(kifmm_plan* P, NearKind kind, hipStream_t s, const std::function<
     KIFMM_HIP(hipStreamWaitEvent(t, P->nearq.fork, 0));
     const bool prof = P->opt.profile && P->events.made;
     if (prof) KIFMM_HIP(hipEventRecord(P->events.p2p[P->events.cur][0], t));
-    first(t);
-    KIFMM_HIP(hipEventRecord(P->nearq.mid, t));
+    if (first) {
+        first(t);
+        KIFMM_HIP(hipEventRecord(P->nearq.mid, t));
+    }
     if (prof) KIFMM_HIP(hipEventRecord(P->events.p2p[P->events.cur][1], t));
     if (kind == NEAR_BACKWARD || kind == NEAR_BACKWARD_EXCL) launch_p2p_backward(P, t, kind == NEAR_BACKWARD_EXCL);
     else if (kind == NEAR_DIPOLES) launch_p2p_dipoles(P, t);

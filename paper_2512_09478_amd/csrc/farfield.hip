@@ -1625,8 +1625,8 @@ void launch_m2m(kifmm_plan* P, int level, const uint4* ops, const float* phi, fl
 // charges (monopoles), 1 = the adjoint sources (monopoles dL/du, dipoles
 // dL/dE).  With both, M2L carries the two columns through each operator load.
 // `between` (may be empty) runs after P2M: the caller forks the near field there
-// and launches what it is given at the head of that stream, recording
-// nearq.mid behind it.
+// and launches what it is given (nothing without X lists) at the head of that
+// stream, recording nearq.mid behind it.
 template <int NP>
 void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const NearFork& between,
                 const StokesFrames* sf, bool fp32_m2l) {
@@ -1665,7 +1665,7 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
     }
     if (depth < ld) {
         if (rec) record_phase(P, 0, s);
-        if (between) between([](hipStream_t) {});
+        if (between) between(nullptr);
         if (rec) for (int k = 1; k < 5; ++k) record_phase(P, k, s);
         return;
     }
@@ -1685,16 +1685,14 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
     // near-field stream, ahead of the near field.
     const auto p2l = [&](hipStream_t t) {
         for (int r = r0; r < r1; ++r)
-            if (P->n_xboxes > 0)
-                hipLaunchKernelGGL(k_p2l<NP>, dim3(unsigned(P->n_xboxes)), dim3(tpb), 0, t, P->xboxes.as<int>(),
-                                   P->x_off.as<int>(), P->x_idx.as<int>(), P->bx_anchor.as<int4>(),
-                                   P->bx_range.as<int2>(), pts, (r && !stk(r)) ? P->src2.as<float4>() : nullptr,
-                                   stk(r) ? sf->frc : nullptr, surf, op.n, geo,
-                                   P->psi_d.as<float>() + r * stride);
+            hipLaunchKernelGGL(k_p2l<NP>, dim3(unsigned(P->n_xboxes)), dim3(tpb), 0, t, P->xboxes.as<int>(),
+                               P->x_off.as<int>(), P->x_idx.as<int>(), P->bx_anchor.as<int4>(),
+                               P->bx_range.as<int2>(), pts, (r && !stk(r)) ? P->src2.as<float4>() : nullptr,
+                               stk(r) ? sf->frc : nullptr, surf, op.n, geo, P->psi_d.as<float>() + r * stride);
     };
-    const bool aside = between != nullptr;
-    if (aside) between(p2l);
-    else p2l(s);
+    const bool any_x = P->n_xboxes > 0, aside = between && any_x;
+    if (between) between(any_x ? std::function<void(hipStream_t)>(p2l) : nullptr);
+    else if (any_x) p2l(s);
     // upward UC2E of the leaves (every level from ld in one launch), then
     // M2M and UC2E of the non-leaves, deepest level first; no leaf waits on the
     // M2M terms of the children of others
