@@ -54,13 +54,18 @@ constexpr int kNearFill = 1024;
 // matrix products run beside the near field's vector instructions (524,288
 // uniform points, evaluation and adjoint: 2.48 ms with four, 2.58 with three,
 // 2.63 with six, 2.65 uncapped; 262,147 with field gradient 0.77 against 0.77,
-// 0.97 and 1.01 ms).  With many points per leaf the near field is most of the
-// work (8.4M Plummer points, p = 8: 10 of 17 ms) and takes six.
-// The kernels are compiled for six blocks per CU (at most 80 registers), none
-// of them with scratch memory: bounds of seven and eight made six of the eight
-// forms spill.
-constexpr int kNearBlocks = 4, kNearBlocksDense = 6, kNearDense = 64;
+// 0.97 and 1.01 ms).  Leaves of many points make no exception (evaluations with
+// four and with six, ms: 330,000 uniform points, 81 a leaf, 0.48 and 0.55;
+// 500,000 Plummer points, p = 8, 72 a leaf, 1.25 and 1.61; 1M clustered, 93 a
+// leaf, 1.93 and 2.03); where the near field is nearly all the work six gain a
+// little (1M clustered, p = 4, 93 a leaf, 1.62 and 1.52; 8.4M Plummer points
+// 16.98 and 16.88).
+constexpr int kNearBlocks = 4;
 
+// Blocks per CU the kernels are compiled for (at most 80 registers), none of
+// them with scratch memory: bounds of seven and eight made six of the eight
+// forms spill, and more registers leave the M2L no room beside four blocks.
+constexpr int kNearBound = 6;
 
 // The gathers precede everything else of a call on the caller's stream and
 // zero its words: the near field's counter and the maximum of the right-hand
@@ -329,7 +334,7 @@ __device__ inline void near_units(const NearArgs& a, const float4* __restrict__ 
 // EXCL: pairs whose clump keys (ckey, sorted) are equal are left out, which
 // drops the pairs of pebbles of one clump and the self pair.
 template <bool EXCL>
-__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p(NearArgs a, const float4* __restrict__ pts, float cst,
+__global__ __launch_bounds__(256, kNearBound) void k_p2p(NearArgs a, const float4* __restrict__ pts, float cst,
                                              float4* __restrict__ nearv, const int* __restrict__ ckey) {
     __shared__ NearShared<NF_ONE, false, EXCL, 4> sh;
     float4 x;
@@ -357,7 +362,7 @@ __global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p(NearArgs a, const
 
 // Near field of monopoles q_j and dipoles m_j (src2 = (q, m) sorted):
 //   u += q_j/r - m_j.r/r^3,  E = -grad u += r (q_j/r^3 - 3 m_j.r/r^5) + m_j/r^3.
-__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_dip(NearArgs a, const float4* __restrict__ pts,
+__global__ __launch_bounds__(256, kNearBound) void k_p2p_dip(NearArgs a, const float4* __restrict__ pts,
                                                  const float4* __restrict__ src2, float cst,
                                                  float4* __restrict__ nearv) {
     __shared__ NearShared<NF_TWO, true, false, 4> sh;
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_dip(NearArgs a, c
 // - 15 (m.r) r_a r_b / r^7.  (u, E) go to nearv, dE/dx (xx yy zz xy xz yz)
 // to nearg.
 template <bool DIP>
-__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_grad(NearArgs a, const float4* __restrict__ pts,
+__global__ __launch_bounds__(256, kNearBound) void k_p2p_grad(NearArgs a, const float4* __restrict__ pts,
                                                   const float4* __restrict__ src2, float cst,
                                                   float4* __restrict__ nearv, float* __restrict__ nearg) {
     constexpr int CAP = DIP ? NF_TWO : NF_GRAD;
@@ -455,7 +460,7 @@ __global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_grad(NearArgs a, 
 // where E, H come from the charges q and psi, E_psi from monopoles ubar and
 // dipoles Ebar (psi = sum ubar K - Ebar . G).
 template <bool EXCL>
-__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_bwd(NearArgs na, const float4* __restrict__ pts,
+__global__ __launch_bounds__(256, kNearBound) void k_p2p_bwd(NearArgs na, const float4* __restrict__ pts,
                                                     const float4* __restrict__ src2, float cst,
                                                     float4* __restrict__ nearv, const int* __restrict__ ckey) {
     constexpr int CAP = EXCL ? NF_KEYS : NF_TWO;
@@ -536,7 +541,7 @@ __global__ void k_gather_stokes(int64_t N, const float4* __restrict__ xs, const 
 // from stk (sorted); written as cst * u to out (sorted), with the unscaled sum
 // of (r.f)/r^3 (the near part of the pressure, times 4 pi) in the fourth
 // component.
-__global__ __launch_bounds__(256, kNearBlocksDense) void k_p2p_stokes(NearArgs a, const float4* __restrict__ xs,
+__global__ __launch_bounds__(256, kNearBound) void k_p2p_stokes(NearArgs a, const float4* __restrict__ xs,
                                                     const float4* __restrict__ stk, float cst,
                                                     float4* __restrict__ out) {
     __shared__ NearShared<NF_TWO, true, false, 4> sh;
@@ -582,10 +587,9 @@ NearLaunch near_launch(kifmm_plan* P, bool images = true) {
     int parts = 1;
     while (parts < 8 && P->n_items * parts < kNearFill) parts *= 2;
     const int units = int(P->n_items) * parts;
-    const int per_cu = P->N > int64_t(kNearDense) * P->nleaves ? kNearBlocksDense : kNearBlocks;
     return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->n_runs.as<int4>(), P->words.as<int>(),
                                images ? float(P->side) : 0.f},
-                      dim3(unsigned(std::min(units, device_cus() * per_cu)))};
+                      dim3(unsigned(std::min(units, device_cus() * kNearBlocks)))};
 }
 
 }  // namespace
