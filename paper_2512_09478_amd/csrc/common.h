@@ -273,6 +273,7 @@ struct kifmm_plan {
     kifmm::DBuf item_tmp;
     int64_t n_items = 0;
     int64_t n_xboxes = 0;
+    int64_t near_entries = 0;   // entries of the near lists
     // densities: [rhs][B][npad]
     kifmm::DBuf psi_u, phi_u, psi_d, phi_d;
     kifmm::DBuf phi_k;      // compressed M2L: projected upward densities [rhs][B][kp]

@@ -62,6 +62,15 @@ constexpr int kNearFill = 1024;
 // 16.98 and 16.88).
 constexpr int kNearBlocks = 4;
 
+// Units of fewer than so many pairs (estimated from the mean near list) are taken
+// four at a time (see near_units).  us an evaluation and an adjoint, one and
+// four at a time: 3,800 pairs a unit (400,000 uniform points, 64 a leaf) 1407 +
+// 1437 and 1221 + 1321, 11,600 (700,000, 128 a leaf) 1394 + 1494 and 1310 + 1481,
+// 14,000 (1M clustered, 96 a leaf) 2140 + 2500 and 2090 + 2510, 31,800 (524,288
+// uniform) 1156 + 1457 and 1160 + 1556.
+constexpr int kNearChunk = 4;
+constexpr double kNearLight = 16384;
+
 // Blocks per CU the kernels are compiled for (at most 80 registers), none of
 // them with scratch memory: bounds of seven and eight made six of the eight
 // forms spill, and more registers leave the M2L no room beside four blocks.
@@ -156,7 +165,8 @@ struct NearArgs {
     const int4* items;   // two words an item, see k_item_fill
     int units, parts;    // units of work: every item in `parts` equal parts of its targets
     const int4* runs;    // runs of contiguous source points, see k_item_fill
-    int* taken;          // units taken beyond the grid's first round
+    int* taken;          // units taken beyond the grid's first round, ...
+    int chunk;           // ... so many at a time
     float cell;          // periodic cell side (image shifts)
 };
 
@@ -279,14 +289,17 @@ __device__ inline bool near_finish(float (&v)[NV], const NearMap& m, float (*red
 // adds staged source j to the sums v, store(i, v) writes the totals.
 // The next batch of sources is read into registers while the present one is
 // summed.  Blocks take their later units from a counter, so that a grid smaller
-// than the work keeps its balance; a unit's arithmetic does not depend on the
+// than the work keeps its balance, several neighbouring ones at a time where
+// there are many: the counter serves one block in 11 ns, which is longer than
+// small leaves take (100,000 points in a sheet, 6 a leaf, 17,000 units: 188 us
+// one at a time, 90 four at a time).  A unit's arithmetic does not depend on the
 // block that does it.
 template <int CAP, bool TWO, bool KEY, int NV, int UNROLL, class Load, class Pair, class Store>
 __device__ inline void near_units(const NearArgs& a, const float4* __restrict__ pts, const float4* __restrict__ src2,
                                   const int* __restrict__ ckey, NearShared<CAP, TWO, KEY, NV>& sh, Load load,
                                   Pair pair, Store store) {
     const int lane = threadIdx.x & 63;
-    int unit = blockIdx.x;
+    int unit = blockIdx.x, end = unit + 1;   // end: behind the units taken (thread 0)
     int4 i0 = a.items[2 * size_t(unit / a.parts)], i1 = a.items[2 * size_t(unit / a.parts) + 1];
     for (int turn = 0; unit < a.units; turn ^= 1) {
         const int per = (i0.y + a.parts - 1) / a.parts, t0 = (unit % a.parts) * per, nt = min(per, i0.y - t0);
@@ -295,7 +308,14 @@ __device__ inline void near_units(const NearArgs& a, const float4* __restrict__ 
         const int4 d = run[min(lane, nr)];
         const int dn = run[min(lane + 1, nr)].y;
         int next = a.units;
-        if (threadIdx.x == 0 && gridDim.x < unsigned(a.units)) next = int(gridDim.x) + atomicAdd(a.taken, 1);
+        if (threadIdx.x == 0 && gridDim.x < unsigned(a.units)) {
+            if (unit + 1 < end) {
+                next = unit + 1;
+            } else {
+                next = int(gridDim.x) + atomicAdd(a.taken, a.chunk);
+                end = next + a.chunk;
+            }
+        }
         const NearMap nm = near_map(i0.x + t0, max(nt, 1));
         load(nm.i, nm.act && nt > 0);
         float v[NV];
@@ -587,9 +607,12 @@ NearLaunch near_launch(kifmm_plan* P, bool images = true) {
     int parts = 1;
     while (parts < 8 && P->n_items * parts < kNearFill) parts *= 2;
     const int units = int(P->n_items) * parts;
+    const int blocks = std::min(units, device_cus() * kNearBlocks);
+    const double leaf = double(P->N) / double(P->nleaves), lists = double(P->near_entries) / double(P->nleaves);
+    const bool light = std::min(64.0, leaf) * lists * leaf < kNearLight;
     return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->n_runs.as<int4>(), P->words.as<int>(),
-                               images ? float(P->side) : 0.f},
-                      dim3(unsigned(std::min(units, device_cus() * kNearBlocks)))};
+                               light ? std::max(1, std::min(kNearChunk, units / (2 * blocks))) : 1, images ? float(P->side) : 0.f},
+                      dim3(unsigned(blocks))};
 }
 
 }  // namespace

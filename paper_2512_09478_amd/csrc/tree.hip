@@ -1845,6 +1845,7 @@ void build_tree(kifmm_plan* P, const double* positions, hipStream_t s) {
     P->nleaves = nl;
     P->n_xboxes = nxb;
     P->n_items = ni;
+    P->near_entries = nn;
     // leaf work items, heaviest first
     {
         P->item_tmp.ensure(size_t(ni) * (32 + 8 + 4 * 8 + 4 * 4) + 1024);
