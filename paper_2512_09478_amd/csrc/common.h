@@ -266,7 +266,9 @@ struct kifmm_plan {
     kifmm::DBuf u_off, u_idx, w_off, w_idx, x_off, x_idx;   // CSR over boxes, int32
     kifmm::DBuf xflag;   // [B + 1] int32: 1 for the boxes the P2L kernel writes (X lists not summed directly)
     kifmm::DBuf n_off, n_idx;   // near lists: U plus the W/X pairs summed point to point
-    kifmm::DBuf n_runs;         // the same as runs of contiguous points (int4, see k_item_fill)
+    const int4* runs = nullptr; // the same as runs of contiguous points (see k_item_fill): behind the entries
+                                // in n_idx, or where they do not fit there in n_runs
+    kifmm::DBuf n_runs;
     kifmm::DBuf wf_off, wf_idx; // W lists of the leaf evaluation (the other W pairs)
     kifmm::DBuf xboxes;     // int32 boxes with a non-empty X list
     kifmm::DBuf items_near, items_far;   // work items (int4[2], see k_item_fill; int2 (leaf, first target)), heaviest first

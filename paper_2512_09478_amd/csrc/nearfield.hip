@@ -610,7 +610,7 @@ NearLaunch near_launch(kifmm_plan* P, bool images = true) {
     const int blocks = std::min(units, device_cus() * kNearBlocks);
     const double leaf = double(P->N) / double(P->nleaves), lists = double(P->near_entries) / double(P->nleaves);
     const bool light = std::min(64.0, leaf) * lists * leaf < kNearLight;
-    return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->n_runs.as<int4>(), P->words.as<int>(),
+    return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->runs, P->words.as<int>(),
                                light ? std::max(1, std::min(kNearChunk, units / (2 * blocks))) : 1, images ? float(P->side) : 0.f},
                       dim3(unsigned(blocks))};
 }
