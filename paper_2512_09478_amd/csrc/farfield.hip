@@ -601,12 +601,18 @@ constexpr int chain_waves(int np, bool wide) {
     return np == 32 ? 2 : np == 64 ? 4 : np == 128 ? (wide ? 8 : 4) : np == 160 ? (wide ? 10 : 5) : np == 224 ? 7 : 10;
 }
 
-template <int NP, int WV, int CB, int KP, bool DOWN, bool STK>
+// MM (upward, non-leaves): psi is the M2M sum over the box's children, formed
+// here in k_m2m's order.  Levels of few boxes with few surface points are launch
+// times, and one launch a level is half of two: up to 64 surface points and kC2eOne
+// boxes, upward pass of 30,000 uniform points (p = 3) 69 us in two launches a
+// level and 46 in one, of 100,000 points in a thin sheet (p = 2, eight levels) 82
+// and 57.
+template <int NP, int WV, int CB, int KP, bool DOWN, bool STK, bool MM = false>
 __global__ __launch_bounds__(64 * WV) void k_c2e(int nblk, int b0, int nb, const int* __restrict__ list,
                                                  const int2* __restrict__ child, const float* __restrict__ psi,
                                                  int nsplit, size_t split_stride, const float* __restrict__ xpsi,
                                                  const int* __restrict__ xflag, const uint4* __restrict__ qc,
-                                                 const uint4* __restrict__ l2l, const uint4* __restrict__ w1c,
+                                                 const uint4* __restrict__ l2l /* MM: m2m */, const uint4* __restrict__ w1c,
                                                  const uint4* __restrict__ vc, float* phi,
                                                  const int4* __restrict__ anchor, BoxGeom geo,
                                                  const float* __restrict__ s0, const float* __restrict__ s1,
@@ -704,6 +710,68 @@ __global__ __launch_bounds__(64 * WV) void k_c2e(int nblk, int b0, int nb, const
                                                                       (wave * NR + i) * 16 + g4);
                     acc[i][cb] += v4f{v.x, v.y, v.z, v.w};
                 }
+    } else if constexpr (MM) {
+        static_assert(!DOWN && !STK, "the M2M sum of a box's children");
+        int2 ch[CB];
+        int mask = 0, flags = 0;   // flags: the octants any column has
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            ch[cb] = tgt[cb] >= 0 ? child[tgt[cb]] : make_int2(0, 0);
+            mask |= ch[cb].y;
+        }
+#pragma unroll
+        for (int o2 = 0; o2 < 8; ++o2)
+            if (__ballot((mask >> o2) & 1)) flags |= 1 << o2;
+#pragma unroll
+        for (int i = 0; i < NR; ++i)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) acc[i][cb] = v4f{0.f, 0.f, 0.f, 0.f};
+        while (flags) {   // two octants read at once
+            int oc[2];
+            uint4 a[2][KC][NR][2];
+            float b[2][CB][KC][8];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                oc[t] = flags ? __builtin_ctz(flags) : -1;
+                flags &= flags - 1;
+                const int o2 = max(oc[t], 0);
+#pragma unroll
+                for (int kc = 0; kc < KC; ++kc) {
+                    const uint4* A = l2l + ((size_t(o2) * KC + kc) * RB + wave * NR) * 128 + lane;
+#pragma unroll
+                    for (int i = 0; i < NR; ++i) {
+                        a[t][kc][i][0] = A[i * 128];
+                        a[t][kc][i][1] = A[i * 128 + 64];
+                    }
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) {
+                        const bool has = oc[t] >= 0 && ((ch[cb].y >> o2) & 1);
+                        const int sb = has ? ch[cb].x + __popc(ch[cb].y & ((1 << o2) - 1)) : 0;
+                        load8(b[t][cb][kc], phi + size_t(sb) * NP + kc * 32 + g8);   // (box 0's where there is no child)
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) b[t][cb][kc][k] = has ? b[t][cb][kc][k] : 0.f;
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                if (oc[t] >= 0)
+#pragma unroll
+                    for (int kc = 0; kc < KC; ++kc)
+#pragma unroll
+                        for (int i = 0; i < NR; ++i) {
+                            const uint4 u0 = a[t][kc][i][0], u1 = a[t][kc][i][1];
+                            const float av[8] = {__uint_as_float(u0.x), __uint_as_float(u0.y), __uint_as_float(u0.z),
+                                                 __uint_as_float(u0.w), __uint_as_float(u1.x), __uint_as_float(u1.y),
+                                                 __uint_as_float(u1.z), __uint_as_float(u1.w)};
+#pragma unroll
+                            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                                for (int cb = 0; cb < CB; ++cb)
+                                    acc[i][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[k], b[t][cb][kc][k],
+                                                                                      acc[i][cb], 0, 0, 0);
+                        }
+        }
     } else {
 #pragma unroll
         for (int i = 0; i < NR; ++i)
@@ -1571,7 +1639,7 @@ void with_kp(const kifmm_plan* P, F f) {
 
 // Check-to-equivalent map of the boxes list[b0 .. b0+nb) (upward) or of their
 // children (downward).
-template <int NP, int KP, bool DOWN, bool STK>
+template <int NP, int KP, bool DOWN, bool STK, bool MM = false>
 void launch_c2e(kifmm_plan* P, const int* list, int64_t b0, int64_t nb, const float* psi, size_t split_stride,
                 const float* xpsi, const uint4* l2l, const uint4* w1c, const uint4* vc, float* phi,
                 const float* const* stk3, hipStream_t s) {
@@ -1584,13 +1652,17 @@ void launch_c2e(kifmm_plan* P, const int* list, int64_t b0, int64_t nb, const fl
     do {                                                                                                            \
         constexpr int WV = chain_waves(NP, WIDE);                                                                   \
         const int blocks = nblk(nb, 16 * CBV) * (DOWN ? 8 : 1);                                                     \
-        hipLaunchKernelGGL((k_c2e<NP, WV, CBV, KP, DOWN, STK>), dim3(unsigned(blocks)), dim3(64 * WV), 0, s, blocks, \
+        hipLaunchKernelGGL((k_c2e<NP, WV, CBV, KP, DOWN, STK, MM>), dim3(unsigned(blocks)), dim3(64 * WV), 0, s, blocks, \
                            int(b0), int(nb), list, P->bx_child.as<int2>(), psi, P->m2l_split_used, split_stride,    \
                            xpsi, P->xflag.as<int>(), KP ? P->cm->q.as<uint4>() : nullptr, l2l, w1c, vc, phi,        \
                            P->bx_anchor.as<int4>(), geo, s3[0], s3[1], s3[2]);                                      \
     } while (0)
-    if (boxes <= kC2eOne) KIFMM_C2E(true, 1);
-    else KIFMM_C2E(false, 2);
+    if constexpr (MM) {
+        KIFMM_C2E(true, 1);   // (boxes <= kC2eOne)
+    } else {
+        if (boxes <= kC2eOne) KIFMM_C2E(true, 1);
+        else KIFMM_C2E(false, 2);
+    }
 #undef KIFMM_C2E
 }
 
@@ -1707,8 +1779,16 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
         };
         c2e(P->leaves.as<int>(), lf0, P->nleaves - lf0);
         for (int l = depth; l >= ld; --l) {
+            const LevelInfo& li = P->lev[l];
+            if constexpr (NP <= 64)
+                if (!stk(r) && li.nl_count <= kC2eOne) {
+                    launch_c2e<NP, 0, false, false, true>(P, P->nonleaf.as<int>(), li.nl_start, li.nl_count, nullptr, 0,
+                                                          nullptr, op.m2m.as<uint4>(), op.uc2e_w1.as<uint4>(),
+                                                          op.uc2e_v.as<uint4>(), phi, nullptr, s);
+                    continue;
+                }
             launch_m2m<NP>(P, l, op.m2m.as<uint4>(), phi, psi, stk(r) ? sf->up : nullptr, s);
-            c2e(P->nonleaf.as<int>(), P->lev[l].nl_start, P->lev[l].nl_count);
+            c2e(P->nonleaf.as<int>(), li.nl_start, li.nl_count);
         }
     }
     // periodic root: every image beyond the root's neighbours
