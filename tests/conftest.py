@@ -11,3 +11,13 @@ if ROOT not in sys.path:
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs an MI355X (run through the HIP library)")
     config.addinivalue_line("markers", "slow: long-running CPU test")
+
+
+@pytest.hookimpl(tryfirst=True)
+def pytest_runtest_setup(item):
+    """Name every GPU test on the terminal before its first GPU step: an abort
+    inside a GPU call then leaves its test's name as the last line printed."""
+    terminal = item.config.pluginmanager.get_plugin("terminalreporter")
+    if item.get_closest_marker("gpu") and terminal is not None and terminal.verbosity <= 0:
+        terminal.write_line("gpu: " + item.nodeid)
+        terminal.flush()
