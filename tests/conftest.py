@@ -14,7 +14,7 @@ def pytest_configure(config):
 
 
 @pytest.hookimpl(tryfirst=True)
-def pytest_runtest_setup(item):
+def pytest_runtest_protocol(item, nextitem):   # (before the output of the test is captured)
     """Name every GPU test on the terminal before its first GPU step: an abort
     inside a GPU call then leaves its test's name as the last line printed."""
     terminal = item.config.pluginmanager.get_plugin("terminalreporter")
