@@ -2,7 +2,8 @@
 // zone), written sorted as a float4 per point; the leaf-evaluation kernel adds
 // it to the far field and writes the caller-order outputs.
 //
-// Work items of at most 64 targets of one leaf, heaviest first.  An item with
+// Work items of at most 64 targets of one leaf, heaviest first (a few in leaf
+// order), taken off a counter by the blocks of a persistent grid.  An item with
 // 16 or more targets gives each of its four waves a quarter of the targets and
 // all of the sources; a smaller item gives every wave all of its targets and
 // every fourth group of sources.  Inside a wave a target has
@@ -13,8 +14,8 @@
 // The source points are streamed through LDS as float4 (x, y, z, q) in global
 // FP32 coordinates, so every pair difference is a correctly rounded FP32
 // subtraction of the input coordinates.  Pairs at distance exactly zero (the
-// self pair, coincident points) are skipped: the leaf's own points are tested
-// pair by pair; between leaves two points meet only where their FP32
+// self pair, coincident points) are skipped: the leaf's own points, the last of
+// its sources, are tested pair by pair; between leaves two points meet only where their FP32
 // coordinates round to one face, so those pairs run untested and an item whose
 // sum comes out infinite or NaN is done again with every pair tested.
 // The kernels are bound by VALU issue (14 instructions per untested pair
@@ -22,10 +23,10 @@
 // a wave copies 64 staged positions at a time out of the runs of contiguous
 // points that the tree build leaves, and the next batch is read while one is
 // summed.  Reading box by box between barriers left the waves waiting for 58 %
-// of their time (1M clustered points, alone with the chip full: 0.84 ms forward
-// and 1.36 ms backward; now 0.60 and 1.07 ms, 42 and 23 TFLOP/s at 20 FLOP per
-// pair: 3 sub, 5 for r^2, rsqrt, 4 for q/r and q/r^3, 7 for the four sums; the
-// forward launch alone, at the four blocks per CU it takes, 0.80 ms).
+// of their time (1M clustered points, alone: 0.84 ms forward and 1.36 ms
+// backward with eight blocks per CU; now 0.75 and 1.07 with six, and 0.80 and
+// 1.16 with the four it takes: 31 TFLOP/s forward at 20 FLOP per pair: 3 sub, 5
+// for r^2, rsqrt, 4 for q/r and q/r^3, 7 for the four sums).
 #include <float.h>
 #include <math.h>
 
