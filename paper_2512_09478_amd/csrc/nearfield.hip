@@ -64,7 +64,11 @@ constexpr int kNearFill = 1024;
 constexpr int kNearBlocks = 4;
 
 // Units of fewer than so many pairs (estimated from the mean near list) are taken
-// four at a time (see near_units).  us an evaluation and an adjoint, one and
+// four at a time (see near_units), or as many as a block has on average where
+// that is fewer: 4,093 units over 1,024 blocks (100,000 points in a sheet, 24 a
+// leaf, p = 4) took 189 us an evaluation one at a time, since each round of the
+// blocks is then as long as the counter serves them (11 us), and 169 three at a
+// time; half as many is no better at any size measured.  us an evaluation and an adjoint, one and
 // four at a time: 3,800 pairs a unit (400,000 uniform points, 64 a leaf) 1407 +
 // 1437 and 1221 + 1321, 11,600 (700,000, 128 a leaf) 1394 + 1494 and 1310 + 1481,
 // 14,000 (1M clustered, 96 a leaf) 2140 + 2500 and 2090 + 2510, 31,800 (524,288
@@ -612,7 +616,7 @@ NearLaunch near_launch(kifmm_plan* P, bool images = true) {
     const double leaf = double(P->N) / double(P->nleaves), lists = double(P->near_entries) / double(P->nleaves);
     const bool light = std::min(64.0, leaf) * lists * leaf < kNearLight;
     return NearLaunch{NearArgs{P->items_near.as<int4>(), units, parts, P->runs, P->words.as<int>(),
-                               light ? std::max(1, std::min(kNearChunk, units / (2 * blocks))) : 1, images ? float(P->side) : 0.f},
+                               light ? std::max(1, std::min(kNearChunk, units / blocks)) : 1, images ? float(P->side) : 0.f},
                       dim3(unsigned(blocks))};
 }
 
