@@ -49,6 +49,9 @@ constexpr int WAVES = 4;
 constexpr int kC2eOne = 4096;
 constexpr int kM2mFew = 1024;
 
+// points up to which P2L stays on the caller's stream at p = 2 (see sweep_impl)
+constexpr int kP2lInline = 1024;
+
 struct BoxGeom {
     double lo[3];
     double side;
@@ -1762,9 +1765,14 @@ void sweep_impl(kifmm_plan* P, int r0, int r1, hipStream_t s, bool rec, const Ne
                                P->bx_range.as<int2>(), pts, (r && !stk(r)) ? P->src2.as<float4>() : nullptr,
                                stk(r) ? sf->frc : nullptr, surf, op.n, geo, P->psi_d.as<float>() + r * stride);
     };
-    const bool any_x = P->n_xboxes > 0, aside = between && any_x;
-    if (between) between(any_x ? std::function<void(hipStream_t)>(p2l) : nullptr);
-    else if (any_x) p2l(s);
+    // P2L beside the upward pass, but for systems so small that making the
+    // launches takes longer than running them: there the event and the wait cost
+    // more (us an evaluation, beside and not: p = 2, thin sheets of 100, 300 and
+    // 1,000 points 71 and 59, 76 and 68, 86 and 77; 2,000 clustered 106 and 117;
+    // p = 4, 1,000 clustered 98 and 105)
+    const bool any_x = P->n_xboxes > 0, aside = between && any_x && !(NP <= 32 && P->N <= kP2lInline);
+    if (between) between(aside ? std::function<void(hipStream_t)>(p2l) : nullptr);
+    if (any_x && !aside) p2l(s);
     // upward UC2E of the leaves (every level from ld in one launch), then
     // M2M and UC2E of the non-leaves, deepest level first; no leaf waits on the
     // M2M terms of the children of others
