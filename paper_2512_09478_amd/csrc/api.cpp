@@ -103,7 +103,8 @@ enum NearKind { NEAR_FORWARD, NEAR_BACKWARD, NEAR_DIPOLES, NEAR_GRAD, NEAR_GRAD_
 // The near field does not depend on the far-field sweep: it runs on the side
 // stream, forked from `s` after P2M (so that the sweep's first kernel is not
 // queued behind it) and joined back before the leaf evaluation, which adds it
-// to the far field.  Neither does P2L (`first`, empty without X lists), which
+// to the far field.  Neither does P2L (`first`; empty where there is none or it
+// stays on `s`), which
 // goes ahead of it there:
 // on the caller's stream it added 50 to 90 us between the upward pass and the
 // M2L.
